@@ -453,21 +453,25 @@ struct ApplyParams {
 };
 
 // A[r][ci+b+q] -= sum_l Y[r][l] Wi[l][q] for rows r >= ci; one thread per row
-// so that every access to At (column-major A) is coalesced.
+// so that every access to At (column-major A) is coalesced.  The sums run over
+// MAX_PANEL rows of Wi; those past the panel's b are zeros in LDS (left as
+// they were they could hold NaN patterns of other kernels, and 0 * NaN would
+// reach A).
 __global__ __launch_bounds__(256) void qr_inner_apply_kernel(ApplyParams p) {
-  __shared__ float Ws[MAX_B * NB];
+  __shared__ float Ws[MAX_PANEL * NB];
   const int64_t bz = blockIdx.y;
   float *At = p.At + bz * p.sA;
   const float *Wi = p.Wi + bz * p.sW;
   const int n = p.n, ci = p.ci, b = p.b, w = p.w;
   const int t = threadIdx.x;
   stage_block<256>(Ws, NB, Wi, w, b, w);
+  for (int e = b * NB + t; e < MAX_PANEL * NB; e += 256) Ws[e] = 0.f;
   __syncthreads();
   const int r = ci + blockIdx.x * 256 + t;
   if (r >= n) return;
-  float y[MAX_B];
+  float y[MAX_PANEL];
 #pragma unroll
-  for (int l = 0; l < MAX_B; ++l) y[l] = (l < b) ? At[(int64_t)(ci + l) * n + r] : 0.f;
+  for (int l = 0; l < MAX_PANEL; ++l) y[l] = (l < b) ? At[(int64_t)(ci + l) * n + r] : 0.f;
   float *dst = At + (int64_t)(ci + b) * n + r;
   int q = 0;
   for (; q + 8 <= w; q += 8) {
@@ -475,7 +479,7 @@ __global__ __launch_bounds__(256) void qr_inner_apply_kernel(ApplyParams p) {
 #pragma unroll
     for (int u = 0; u < 8; ++u) { cur[u] = dst[(int64_t)(q + u) * n]; s[u] = 0.f; }
 #pragma unroll
-    for (int l = 0; l < MAX_B; ++l)
+    for (int l = 0; l < MAX_PANEL; ++l)
 #pragma unroll
       for (int u = 0; u < 8; ++u) s[u] += y[l] * Ws[l * NB + q + u];
 #pragma unroll
@@ -484,7 +488,7 @@ __global__ __launch_bounds__(256) void qr_inner_apply_kernel(ApplyParams p) {
   for (; q < w; ++q) {
     float s = 0.f;
 #pragma unroll
-    for (int l = 0; l < MAX_B; ++l) s += y[l] * Ws[l * NB + q];
+    for (int l = 0; l < MAX_PANEL; ++l) s += y[l] * Ws[l * NB + q];
     dst[(int64_t)q * n] -= s;
   }
 }

@@ -292,3 +292,29 @@ def test_checkpoint_resume_is_bitwise(kl, batch):
     a, b = run(), run(stop=k)
     for key in a:
         assert np.array_equal(a[key], b[key]), key
+
+
+def test_panel_path_ignores_what_other_kernels_left_in_lds():
+    """64 matrices take the QR's panel path; the step after products of NaN
+    matrices (whose LDS holds NaN on every compute unit) is bit for bit the
+    step before them."""
+    import torch
+    import paper_2607_20548_amd as soap
+    batch, m, n = 64, 300, 260
+    g = torch.Generator(device="cuda").manual_seed(5)
+    G = 0.01 * torch.randn(batch, m, n, generator=g, device="cuda")
+    nans = torch.full((4096, 4096), float("nan"), device="cuda")
+    out = []
+    for litter in (False, True):
+        st = soap.SoapState(m, n, batch=batch)
+        W = torch.zeros(batch, m, n, device="cuda")
+        if litter:
+            for _ in range(4):
+                nans @ nans
+                nans.to(torch.bfloat16) @ nans.to(torch.bfloat16)
+        st.step(W, G, 1, **HP)
+        out.append([t.clone() for t in (W, st.Q_L, st.Q_R, st.V)])
+    torch.cuda.synchronize()
+    for a, b in zip(*out):
+        assert torch.isfinite(a).all()
+        assert torch.equal(a, b)
