@@ -1,21 +1,30 @@
-// fp32 GEMM on the CDNA4 matrix cores (v_mfma_f32_32x32x2_f32), used for every
-// dense product of the SOAP step: the factor EMAs (one triangle), the power
-// products L Q_L and R Q_R, the rotations and the compact-WY updates of the QR.
+// fp32 GEMM on the CDNA4 matrix cores, used for every dense product of the
+// SOAP step: the factor EMAs (one triangle), the power products L Q_L and
+// R Q_R, the rotations and the compact-WY updates of the QR.
+//
+// Arithmetic: each fp32 operand is split into three bfloat16 parts,
+// x = hi + mid + lo (exact: 3 x 8 bits and the parts' signs cover the 24 bits),
+// and a product takes the six partial products above 2^-27 of the largest on
+// v_mfma_f32_32x32x16_bf16, which run at 16 times the rate of the fp32 matrix
+// instructions (six of them: 2.7 times).  bfloat16 products are exact in fp32;
+// the sums of one K slab start from zero and are added to the fp32
+// accumulators on the vector unit.  Left in the matrix instructions' own
+// accumulator, a long sum of one sign lost 1.2e-5 (K = 6144), because they
+// cut addends off below its last bits; as it is, the error against fp64 is
+// 2.2e-7 at 4096^3 and 3.1e-7 at 8192^3 (Gaussian operands), against 1.15e-6
+// and 1.6e-6 on v_mfma_f32_32x32x2_f32.  Operands are split once, on the way
+// to LDS.  Parts that would fall outside bfloat16's range are handled after the
+// K loop (see there).
+// Measured: 4096^3 1150 -> 850 us and 14336^3 (both operands x-contiguous)
+// 44.0 -> 35.2 ms against the fp32 instructions, i.e. 167-183 TFLOP/s
+// of products, 1.0-1.1 PFLOP/s of bfloat16 matrix work; the same launches on
+// zero operands run at 205-234, so that the card's power bounds the large
+// products (a large library product in bfloat16 runs at 1.37 PFLOP/s).
 //
 // Tiling: a 256-thread workgroup (4 wave64s in a 2 x 2 arrangement) computes a
-// 128 x 128 tile of C; each wave owns a 64 x 64 sub-tile held as 2 x 2 MFMA
-// 32x32 accumulators (64 accumulation registers per lane).  K advances in slabs
-// of 16 staged through double-buffered LDS; the global loads run two slabs
-// ahead in two register sets (also for the rank-k updates, whose few slabs
-// would otherwise each wait for their loads), with every load issued
-// unconditionally at a clamped address so that the waits cover exactly the
-// slab being stored.  Both operands are kept in LDS as
-// [x][k] rows (x = output row or column, k contiguous, padded to 20 floats so
-// that 16-byte reads of 16 consecutive lanes fall in distinct banks); a lane
-// then fetches the 8 k-values it feeds to 8 consecutive MFMAs with two
-// ds_read_b128.  Within a 16-slab, lane half h of the MFMA operand carries
-// k = 8h + s at MFMA step s; A and B use the same assignment, so the sum over
-// k is complete.
+// 128 x 128 tile of C; each wave owns a 64 x 64 sub-tile held as 2 x 2 32x32
+// accumulators.  K advances in slabs of 32; the global loads of the next slab
+// are in flight while a slab is multiplied.
 //
 // Epilogue: the tile goes through LDS (free after the K loop) so that C is read
 // and written 16 bytes per lane (see the epilogue).
@@ -30,23 +39,34 @@ namespace soap {
 namespace {
 
 typedef float v16f __attribute__((ext_vector_type(16)));
+typedef float v2f __attribute__((ext_vector_type(2)));
+typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 
 constexpr int BM = 128;
 constexpr int BN = 128;
-constexpr int BK = 16;
-constexpr int LDSK = BK + 4;            // padded LDS row stride in floats ([x][k] rows)
-constexpr int TILE_FLOATS = 128 * LDSK;  // one operand tile in LDS
-// [k][x] rows of an x-contiguous operand (vector path): 128 x-values padded to
-// 132 floats, so that the two lane halves of a fragment read (k and k + 8)
-// fall in disjoint banks.
-constexpr int LDSX = BN + 4;
-static_assert(BK * LDSX <= TILE_FLOATS, "an x-contiguous slab must fit one tile buffer");
+constexpr int BK = 32;
 constexpr int NTHREADS = 256;
-constexpr int SHORT_K = 512;    // products with at most this much K per slice use the rank-k kernel
 constexpr int GROUP_M = 8;
 
+// LDS image of one operand slab (128 x-rows, 32 k): three bfloat16 planes; in
+// a plane the 16-byte unit (x, g) holds k = 8 g .. 8 g + 7 of row x, at
+// g * LDS_G + (x / 2) * 16 + (x % 2) * LDS_ODD.  A fragment read (one g, 32
+// consecutive x) then covers all banks every eight lanes, and so do the
+// writes of both loaders (x pairs of one g; four g of two rows).
+constexpr int LDS_ODD = 64 * 16 + 64;
+constexpr int LDS_G = 2 * LDS_ODD + 16;
+constexpr int LDS_PLANE = 4 * LDS_G;
+constexpr int LDS_OPERAND = 3 * LDS_PLANE;
+
+// Sums below this (2^-90, as bits) are taken again in fp32.
+constexpr uint32_t EXACT_BELOW = (127u - 90u) << 23;
 
 enum { MODE_GENERAL = 0, MODE_SYRK = 1, MODE_ADAM = 2 };
+// How an operand is read: V_ALIGNED with 16-byte (k-contiguous) or 8-byte
+// (x-contiguous) aligned loads and whole quads / pairs, V_ANY the same loads
+// at 4-byte alignment with the ragged ends handled.
+enum { V_ALIGNED = 0, V_ANY = 1 };
 
 struct KParams {
   int M, N, K;
@@ -67,159 +87,130 @@ struct KParams {
   int64_t sSkip;
 };
 
-// Loads one operand slab of 128 x-rows by BK k-values into registers.
-//   KCONTIG = true : global element (x, k) at base[x*ld + k]
-//   KCONTIG = false: global element (x, k) at base[k*ld + x]
-// Work split: 512 (x, k-quad) items over 256 threads, two per thread; with
-// VEC == 4 an x-contiguous slab is instead read either as 4 x 2 blocks
-// (k-quad, x pair; 8-byte loads), one per thread, transposed in registers to
-// [x][k] rows, or (KX) as 512 (k, x-quad) items with 16-byte loads, each wave
-// covering two k rows per load instruction, kept in LDS as [k][x] rows
-// exactly as loaded.  The rank-k kernel takes the second form (5-7% faster
-// at K = 128-512: the register copies of the transposition had made its
-// loads wait right after their issue); for the long-K kernel it measured 1%
-// slower (its fragments then need eight 4-byte LDS reads instead of two
-// 16-byte ones).
-template <bool KCONTIG, int VEC, bool KX = false>
-struct SlabLoader {
-  float r[8];
+__device__ __forceinline__ int lds_unit(int x, int g) {
+  return g * LDS_G + (x >> 1) * 16 + (x & 1) * LDS_ODD;
+}
 
-  // Every load is issued unconditionally at an address clamped into the
-  // matrix: with no branch around the loads the compiler can wait for exactly
-  // the loads a store needs, which the two-slab prefetch of the long-K loop
-  // relies on.  With VEC == 4 the values are used as loaded: rows x >= X only
-  // reach output rows or columns that are never written, and k-values past
-  // the end of K are zeroed by store() (kvalid), right before they go to LDS,
-  // so that nothing consumes a loaded register early.  The scalar path
-  // (VEC == 1) masks both at load time.  Requires X >= 1, K >= 1 (and the
-  // VEC == 4 preconditions: K % 4 == 0 for k-contiguous, X even for
-  // x-contiguous operands, and with KX X % 4 == 0 and a leading dimension
-  // and base aligned to 16 bytes).
+struct f4u { float x, y, z, w; };   // 4-byte aligned
+struct f2u { float x, y; };
+
+// Two floats as three bfloat16 pairs with x = hi + mid + lo exactly (for
+// |x| from about 2^-102 to the largest bfloat16): each part is the remainder
+// rounded to nearest, so mid <= 2^-9 |x| and lo <= 2^-18 |x|.
+__device__ __forceinline__ void split2(float x0, float x1, uint32_t &hi, uint32_t &mid,
+                                       uint32_t &lo) {
+  const v2f v = {x0, x1};
+  hi = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, v2bf));
+  const float r0 = x0 - __uint_as_float(hi << 16);
+  const float r1 = x1 - __uint_as_float(hi & 0xffff0000u);
+  const v2f r = {r0, r1};
+  mid = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, v2bf));
+  const v2f q = {r0 - __uint_as_float(mid << 16), r1 - __uint_as_float(mid & 0xffff0000u)};
+  lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(q, v2bf));
+}
+
+// Splits eight consecutive k of row x and writes them as unit (x, g).
+__device__ __forceinline__ void store_unit(char *lds, int x, int g, const float (&v)[8]) {
+  uint4 h, m, l;
+  split2(v[0], v[1], h.x, m.x, l.x);
+  split2(v[2], v[3], h.y, m.y, l.y);
+  split2(v[4], v[5], h.z, m.z, l.z);
+  split2(v[6], v[7], h.w, m.w, l.w);
+  char *dst = lds + lds_unit(x, g);
+  *reinterpret_cast<uint4 *>(dst) = h;
+  *reinterpret_cast<uint4 *>(dst + LDS_PLANE) = m;
+  *reinterpret_cast<uint4 *>(dst + 2 * LDS_PLANE) = l;
+}
+
+// One operand slab of 128 x-rows by BK k-values: 16 values per thread.
+//   KCONTIG = true : global element (x, k) at base[x*ld + k]; a thread holds
+//     k-octet tid & 3 of rows tid >> 2 and 64 + (tid >> 2)
+//   KCONTIG = false: global element (x, k) at base[k*ld + x]; a thread holds
+//     the k-octet of its wave (tid >> 6) for rows 2 lane, 2 lane + 1
+// Every load is issued unconditionally at an address clamped into the
+// matrix, so nothing consumes a loaded register before store(): rows x >= X
+// only reach output rows or columns that are never written, and k-values
+// past the end of K are zeroed by store().  V_ALIGNED needs K % 4 == 0 (and
+// the row starts 16-byte aligned) for k-contiguous operands and an even X
+// (8-byte aligned rows) for x-contiguous ones.
+template <bool KCONTIG, int LOADS>
+struct SlabLoader {
+  float r[2][8];
+
   __device__ __forceinline__ void load(const float *__restrict__ base, int64_t ld, int x0,
                                        int k0, int X, int K, int tid) {
+    if constexpr (KCONTIG) {
+      const int k = k0 + 8 * (tid & 3);
 #pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const int idx = tid + NTHREADS * s;
-      if (KCONTIG) {
-        const int x = x0 + (idx >> 2);
-        const int k = k0 + 4 * (idx & 3);
-        const int64_t row = (int64_t)min(x, X - 1) * ld;
-        if (VEC == 4) {
-          const float4 v = *reinterpret_cast<const float4 *>(base + row + min(k, K - 4));
-          r[4 * s + 0] = v.x; r[4 * s + 1] = v.y; r[4 * s + 2] = v.z; r[4 * s + 3] = v.w;
-        } else {
+      for (int s = 0; s < 2; ++s) {
+        const float *row = base + (int64_t)min(x0 + (tid >> 2) + 64 * s, X - 1) * ld;
+        if (LOADS == V_ALIGNED) {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float v = base[row + min(k + e, K - 1)];
-            r[4 * s + e] = (x < X && k + e < K) ? v : 0.f;
+          for (int q = 0; q < 2; ++q) {
+            const float4 v = *reinterpret_cast<const float4 *>(row + min(k + 4 * q, K - 4));
+            r[s][4 * q] = v.x; r[s][4 * q + 1] = v.y; r[s][4 * q + 2] = v.z; r[s][4 * q + 3] = v.w;
           }
+        } else if (k0 + BK <= K) {
+#pragma unroll
+          for (int q = 0; q < 2; ++q) {
+            const f4u v = *reinterpret_cast<const f4u *>(row + k + 4 * q);
+            r[s][4 * q] = v.x; r[s][4 * q + 1] = v.y; r[s][4 * q + 2] = v.z; r[s][4 * q + 3] = v.w;
+          }
+        } else {   // the ragged slab (or past the end): element by element
+#pragma unroll
+          for (int e = 0; e < 8; ++e) r[s][e] = row[min(k + e, K - 1)];
         }
-      } else if (VEC == 4 && KX) {
-        // x-contiguous with 16-byte loads: wave w reads k rows 8s + 2w (lanes
-        // 0-31) and 8s + 2w + 1 (lanes 32-63), four consecutive x per lane.
-        // The row address is formed on the scalar unit (k is uniform within
-        // each half wave; the second half adds one row, or none at the end
-        // of K), each lane adds its column offset.
-        const int lane = tid & 63;
-        const int kb = k0 + 8 * s + 2 * __builtin_amdgcn_readfirstlane(tid >> 6);
-        const float *rowp = base + (int64_t)min(kb, K - 1) * ld;
-        const int64_t dr = (kb < K - 1) ? ld : 0;
-        const unsigned xc = (unsigned)min(x0 + 4 * (lane & 31), X - 4);
-        const float4 v = *reinterpret_cast<const float4 *>(rowp + ((lane >> 5) ? dr : 0) + xc);
-        r[4 * s + 0] = v.x; r[4 * s + 1] = v.y; r[4 * s + 2] = v.z; r[4 * s + 3] = v.w;
-      } else if (VEC == 4) {
-        // x-contiguous with 8-byte loads: thread -> (k-quad, x pair); the
-        // 4 x 2 block is transposed in registers (r[0..3] = column x,
-        // r[4..7] = column x+1).  Needs an even x extent and leading
-        // dimension.  k is uniform within a wave, so the row address is
-        // formed on the scalar unit and each lane adds its column offset.
-        if (s == 0) {
-          const int x = x0 + 2 * (tid & 63);
-          const int k = k0 + 4 * __builtin_amdgcn_readfirstlane(tid >> 6);
-          const unsigned xc = (unsigned)min(x, X - 2);
+      }
+    } else {
+      // k is uniform within a wave: the row address is formed on the scalar
+      // unit and each lane adds its column offset.
+      const int k = k0 + 8 * __builtin_amdgcn_readfirstlane(tid >> 6);
+      const int x = x0 + 2 * (tid & 63);
+      if (LOADS == V_ALIGNED || X > 1) {
+        const unsigned xc = (unsigned)min(x, X - 2);
+        // an odd X: the last row is the second of the clamped pair
+        const bool odd = LOADS == V_ANY && x == X - 1;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float *rowp = base + (int64_t)min(k + e, K - 1) * ld;
+        for (int e = 0; e < 8; ++e) {
+          const float *rowp = base + (int64_t)min(k + e, K - 1) * ld;
+          float vx, vy;
+          if (LOADS == V_ALIGNED) {
             const float2 v = *reinterpret_cast<const float2 *>(rowp + xc);
-            r[e] = v.x;
-            r[4 + e] = v.y;
+            vx = v.x; vy = v.y;
+          } else {
+            const f2u v = *reinterpret_cast<const f2u *>(rowp + xc);
+            vx = v.x; vy = v.y;
           }
+          r[0][e] = odd ? vy : vx;
+          r[1][e] = vy;
         }
       } else {
-        const int x = x0 + (idx & 127);
-        const int k = k0 + 4 * (idx >> 7);
-        const int xc = min(x, X - 1);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float v = base[(int64_t)min(k + e, K - 1) * ld + xc];
-          r[4 * s + e] = (x < X && k + e < K) ? v : 0.f;
-        }
+        for (int e = 0; e < 8; ++e) r[0][e] = r[1][e] = base[(int64_t)min(k + e, K - 1) * ld];
       }
     }
   }
 
-  // Writes the slab to LDS, as [x][k] rows ([k][x] rows for an x-contiguous
-  // operand on the vector path); kvalid = number of k-values of this slab
-  // inside K (BK except in the last, ragged slab).
-  __device__ __forceinline__ void store(float *lds, int tid, int kvalid) {
-    if (!KCONTIG && VEC == 4 && KX) {
-      const int lane = tid & 63, w = tid >> 6;
+  // Splits the slab into the LDS planes; kvalid = number of k-values of this
+  // slab inside K (BK except in the last, ragged slab).
+  __device__ __forceinline__ void store(char *lds, int tid, int kvalid) {
+    const int g = KCONTIG ? (tid & 3) : (tid >> 6);
+    if (kvalid < BK) {
 #pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        const int k = 8 * s + 2 * w + (lane >> 5);
-        float4 v = make_float4(r[4 * s + 0], r[4 * s + 1], r[4 * s + 2], r[4 * s + 3]);
-        if (k >= kvalid) v = make_float4(0.f, 0.f, 0.f, 0.f);
-        *reinterpret_cast<float4 *>(lds + k * LDSX + 4 * (lane & 31)) = v;
-      }
-      return;
-    }
-    if (VEC == 4 && kvalid < BK) {
-#pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        const int idx = tid + NTHREADS * s;
-        const int kl = KCONTIG ? 4 * (idx & 3) : 4 * (tid >> 6);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          if (KCONTIG) {
-            if (kl >= kvalid) r[4 * s + e] = 0.f;   // K % 4 == 0: whole quads
-          } else if (s == 0 && kl + e >= kvalid) {
-            r[e] = 0.f;
-            r[4 + e] = 0.f;
-          }
-        }
-      }
-    }
-    if (!KCONTIG && VEC == 4) {
-      const int xl = 2 * (tid & 63), kq = tid >> 6;
-      *reinterpret_cast<float4 *>(lds + xl * LDSK + 4 * kq) = make_float4(r[0], r[1], r[2], r[3]);
-      *reinterpret_cast<float4 *>(lds + (xl + 1) * LDSK + 4 * kq) =
-          make_float4(r[4], r[5], r[6], r[7]);
-      return;
+      for (int e = 0; e < 8; ++e)
+        if (8 * g + e >= kvalid) r[0][e] = r[1][e] = 0.f;
     }
 #pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const int idx = tid + NTHREADS * s;
-      const int x = KCONTIG ? (idx >> 2) : (idx & 127);
-      const int kq = KCONTIG ? (idx & 3) : (idx >> 7);
-      *reinterpret_cast<float4 *>(lds + x * LDSK + 4 * kq) =
-          make_float4(r[4 * s + 0], r[4 * s + 1], r[4 * s + 2], r[4 * s + 3]);
-    }
+    for (int s = 0; s < 2; ++s)
+      store_unit(lds, KCONTIG ? (tid >> 2) + 64 * s : 2 * (tid & 63) + s, g, r[s]);
   }
 };
 
-// The 8 k-values k = 8h + s (s = 0..7) of operand row x from LDS: two 16-byte
-// reads from [x][k] rows, or (KX) eight 4-byte reads from [k][x] rows.
-template <bool KX>
-__device__ __forceinline__ void read_frag(const float *lds, int x, int h, float (&f)[8]) {
-  if constexpr (KX) {
-#pragma unroll
-    for (int s = 0; s < 8; ++s) f[s] = lds[(8 * h + s) * LDSX + x];
-  } else {
-    const float4 lo = *reinterpret_cast<const float4 *>(lds + x * LDSK + 8 * h);
-    const float4 hi = *reinterpret_cast<const float4 *>(lds + x * LDSK + 8 * h + 4);
-    f[0] = lo.x; f[1] = lo.y; f[2] = lo.z; f[3] = lo.w;
-    f[4] = hi.x; f[5] = hi.y; f[6] = hi.z; f[7] = hi.w;
-  }
+// Element (x, k) of an operand, k < K (used by the exact path below).
+template <bool KCONTIG>
+__device__ __forceinline__ float operand_at(const float *base, int64_t ld, int x, int k, int X) {
+  const int xc = min(x, X - 1);
+  return KCONTIG ? base[(int64_t)xc * ld + k] : base[(int64_t)k * ld + xc];
 }
 
 // Maps the linear workgroup id to a (tile-row, tile-column) pair.
@@ -245,14 +236,14 @@ __device__ __forceinline__ void tile_coords(const KParams &p, int t, int &tm, in
   }
 }
 
-// MINB > 1 marks the short-K variant (K per slice <= SHORT_K, the QR's
-// rank-k updates): the bound on resident workgroups makes the compiler keep
-// the accumulators in VGPRs (4 workgroups per CU), and the epilogue batches
-// its reads of C.  Long-K products (MINB = 1) keep the accumulators in AGPRs.
-template <int TA, int TB, int VEC, int MODE, int TAG, int MINB, bool PERSIST = false>
-__global__ __launch_bounds__(NTHREADS, MINB) void gemm_f32_mfma(KParams p) {
-  constexpr bool SHORTK = MINB > 1;
-  __shared__ __attribute__((aligned(16))) float lds[2 * 2 * TILE_FLOATS];
+// Two workgroups per CU (256 registers per lane: accumulators, one or two
+// blocks' slab sums, the slab in flight and the fragments of a block), whose
+// loads, splits and matrix instructions overlap one another; bounded to
+// three, the slab sums spill (180 -> 89 TFLOP/s).
+template <int TA, int TB, int LOADS, int MODE, int TAG, bool PERSIST = false>
+__global__ __launch_bounds__(NTHREADS, 2) void gemm_f32_split(KParams p) {
+  __shared__ __attribute__((aligned(16))) char lds_raw[2 * LDS_OPERAND];
+  float *const lds = reinterpret_cast<float *>(lds_raw);
   if (p.skip && p.skip[(int64_t)blockIdx.z * p.sSkip] != 0u) return;
 
   // One tile per workgroup; PERSIST: a loop over tiles when the grid was
@@ -271,10 +262,8 @@ __global__ __launch_bounds__(NTHREADS, MINB) void gemm_f32_mfma(KParams p) {
 
   // op(A) rows are x = i: k-contiguous when TA == 0.  op(B) columns are x = j:
   // k-contiguous when TB == 1.
-  // the rank-k kernel keeps x-contiguous operands as [k][x] rows in LDS
-  constexpr bool KXL = SHORTK && VEC == 4;
-  SlabLoader<TA == 0, VEC, KXL> la;
-  SlabLoader<TB == 1, VEC, KXL> lb;
+  SlabLoader<TA == 0, LOADS> la;
+  SlabLoader<TB == 1, LOADS> lb;
 
   v16f acc[2][2];
 #pragma unroll
@@ -284,64 +273,101 @@ __global__ __launch_bounds__(NTHREADS, MINB) void gemm_f32_mfma(KParams p) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-  auto buf = [&](int stage, int which) { return lds + (stage * 2 + which) * TILE_FLOATS; };
-
+  char *const sa = lds_raw, *const sb = lds_raw + LDS_OPERAND;
   const int kbeg = blockIdx.y * p.kslice;
   const int kend = min(p.K, kbeg + p.kslice);
   const int nk = (kend - kbeg + BK - 1) / BK;
-  // One K slab from LDS buffer `cur` into the accumulators.
-  constexpr bool AKX = KXL && TA == 1, BKX = KXL && TB == 0;
-  auto compute = [&](int cur) {
-    float fa[2][8], fb[2][8];
-    read_frag<BKX>(buf(cur, 1), wn * 64 + xl, h, fb[0]);
-    read_frag<BKX>(buf(cur, 1), wn * 64 + 32 + xl, h, fb[1]);
-    read_frag<AKX>(buf(cur, 0), wm * 64 + xl, h, fa[0]);
-    read_frag<AKX>(buf(cur, 0), wm * 64 + 32 + xl, h, fa[1]);
+  if (nk > 0) {
+    la.load(A, p.lda, m0, kbeg, p.M, kend, tid);
+    lb.load(B, p.ldb, n0, kbeg, p.N, kend, tid);
+  }
+  for (int kt = 0; kt < nk; ++kt) {
+    const int k0 = kbeg + kt * BK;
+    const int kvalid = min(BK, kend - k0);
+    la.store(sa, tid, kvalid);
+    lb.store(sb, tid, kvalid);
+    __syncthreads();
+    if (kt + 1 < nk) {
+      la.load(A, p.lda, m0, k0 + BK, p.M, kend, tid);
+      lb.load(B, p.ldb, n0, k0 + BK, p.N, kend, tid);
+    }
+    // block by block: the slab's sums from zero, then into the accumulators
+    v8bf fa[2][3], fb[2][3];
+    auto frag = [&](const char *base, int x, v8bf (&f)[2][3]) {
 #pragma unroll
-    for (int s = 0; s < 8; ++s)
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int pl = 0; pl < 3; ++pl)
+          f[q][pl] = __builtin_bit_cast(v8bf, *reinterpret_cast<const uint4 *>(
+              base + pl * LDS_PLANE + lds_unit(x, 2 * q + h)));
+    };
+    auto block = [&](v16f &c) {
+      v16f t;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) t[r] = 0.f;
+      // the six products above 2^-27 of the largest, the small ones first
+#pragma unroll
+      for (int u = 0; u < 6; ++u) {
+        constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+          t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[q][pa[u]], fb[q][pb[u]], t, 0, 0, 0);
+      }
+#pragma unroll
+      for (int r = 0; r < 16; ++r) c[r] += t[r];
+    };
+    frag(sa, wm * 64 + xl, fa);
+    frag(sb, wn * 64 + xl, fb);
+    block(acc[0][0]);
+    frag(sb, wn * 64 + 32 + xl, fb);
+    block(acc[0][1]);
+    frag(sa, wm * 64 + 32 + xl, fa);
+    block(acc[1][1]);
+    frag(sb, wn * 64 + xl, fb);
+    block(acc[1][0]);
+    __syncthreads();
+  }
+
+  // A wave whose sums hold an infinity or a NaN (an infinite operand times a
+  // zero part gives NaN here and not in fp32; so does an operand that
+  // rounds past the largest bfloat16), or whose largest sum is so small that
+  // parts of the operands fell below the smallest bfloat16, takes its sums
+  // again on the fp32 matrix instructions, straight from memory.
+  {
+    uint32_t mx = 0u;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) mx = max(mx, __float_as_uint(acc[i][j][r]) & 0x7fffffffu);
+    const bool big = __any(mx >= 0x7f800000u);
+    const bool tiny = __any(mx != 0u) && !__any(mx >= EXACT_BELOW);
+    if (big || tiny) {
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i][s], fb[j][s], acc[i][j], 0, 0, 0);
-  };
-
-  {
-    // Global loads run two slabs ahead of the matrix cores (two register
-    // sets), so a slab's loads have two slabs of MFMA work to land.
-    SlabLoader<TA == 0, VEC, KXL> lc;
-    SlabLoader<TB == 1, VEC, KXL> ld;
-    auto load_set = [&](SlabLoader<TA == 0, VEC, KXL> &xa, SlabLoader<TB == 1, VEC, KXL> &xb, int kt) {
-      const int k0 = kbeg + kt * BK;
-      xa.load(A, p.lda, m0, k0, p.M, kend, tid);
-      xb.load(B, p.ldb, n0, k0, p.N, kend, tid);
-    };
-    auto store_set = [&](SlabLoader<TA == 0, VEC, KXL> &xa, SlabLoader<TB == 1, VEC, KXL> &xb, int stage,
-                         int kt) {
-      const int kvalid = min(BK, kend - (kbeg + kt * BK));
-      xa.store(buf(stage, 0), tid, kvalid);
-      xb.store(buf(stage, 1), tid, kvalid);
-    };
-    // slab kt is computed from LDS while the register set `held` carries
-    // slab kt+1 (stored to the other buffer after the MFMAs) and `next`
-    // receives slab kt+2.
-    auto body = [&](int kt, SlabLoader<TA == 0, VEC, KXL> &ha, SlabLoader<TB == 1, VEC, KXL> &hb,
-                    SlabLoader<TA == 0, VEC, KXL> &na, SlabLoader<TB == 1, VEC, KXL> &nb) {
-      const int cur = kt & 1;
-      load_set(na, nb, kt + 2);   // past the end: clamped loads, all zero
-      compute(cur);
-      if (kt + 1 < nk) store_set(ha, hb, cur ^ 1, kt + 1);
-      __syncthreads();
-    };
-    if (nk > 0) {
-      load_set(lc, ld, 0);
-      store_set(lc, ld, 0, 0);
-      load_set(la, lb, 1);
-    }
-    __syncthreads();
-    for (int kt = 0; kt < nk; kt += 2) {
-      body(kt, la, lb, lc, ld);
-      if (kt + 1 < nk) body(kt + 1, lc, ld, la, lb);
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+#pragma unroll 1
+      for (int k = kbeg; k < kend; k += 2) {
+        const int kk = min(k + h, kend - 1);
+        const float live = (k + h < kend) ? 1.f : 0.f;
+        float ea[2], eb[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const float va = operand_at<TA == 0>(A, p.lda, m0 + wm * 64 + 32 * i + xl, kk, p.M);
+          const float vb = operand_at<TB == 1>(B, p.ldb, n0 + wn * 64 + 32 * i + xl, kk, p.N);
+          ea[i] = live != 0.f ? va : 0.f;
+          eb[i] = live != 0.f ? vb : 0.f;
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(ea[i], eb[j], acc[i][j], 0, 0, 0);
+      }
     }
   }
 
@@ -351,13 +377,8 @@ __global__ __launch_bounds__(NTHREADS, MINB) void gemm_f32_mfma(KParams p) {
   float *P = p.part ? p.part + (bz * gridDim.y + blockIdx.y) * (int64_t)p.M * p.N : nullptr;
   float *V = (MODE == MODE_ADAM) ? p.V + bz * p.sC : nullptr;
   float *Nout = (MODE == MODE_ADAM) ? p.Nout + bz * p.sC : nullptr;
-  // Short-K products (rank-k updates) spend a large share of their time
-  // here, so their C values are loaded 16 at a time before any store (the
-  // compiler cannot move a load of C above a store to C, and reading one
-  // element after storing the previous one serializes 64 memory latencies).
-  // Long-K products keep the register-lean element-by-element form.
   bool staged = false;
-  if constexpr (MODE == MODE_SYRK && !SHORTK) {
+  if constexpr (MODE == MODE_SYRK) {
    if ((reinterpret_cast<uintptr_t>(C) & 15u) == 0 && (p.ldc & 3) == 0) {
     staged = true;
     // One triangle, mirrored, through LDS in two halves of 64 rows: the
@@ -528,37 +549,6 @@ __global__ __launch_bounds__(NTHREADS, MINB) void gemm_f32_mfma(KParams p) {
   }
   if (staged) {
     // done
-  } else if constexpr (SHORTK) {
-   {
-    const bool read_back = !P && p.beta != 0.f;
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int col = n0 + wn * 64 + j * 32 + xl;
-        float cv[16];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int row = m0 + wm * 64 + i * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
-          const int64_t off = (int64_t)row * p.ldc + col;
-          cv[r] = 0.f;
-          if (read_back && row < p.M && col < p.N) cv[r] = C[off];
-        }
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int row = m0 + wm * 64 + i * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
-          if (row >= p.M || col >= p.N) continue;
-          const int64_t off = (int64_t)row * p.ldc + col;
-          if (P) {
-            P[(int64_t)row * p.N + col] = acc[i][j][r];
-          } else {
-            float v = p.alpha * acc[i][j][r];
-            if (p.beta != 0.f) v += p.beta * cv[r];
-            C[off] = v;
-          }
-        }
-      }
-   }
   } else {
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -636,11 +626,43 @@ __global__ __launch_bounds__(256) void splitk_reduce(const float *__restrict__ p
 
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-// vec_ok, vec_ok_kx: the vector path's preconditions for the long-K kernel
-// and for the rank-k kernel (vec_ok_for).
+template <int MODE, int TAG, bool PERSIST>
+hipError_t launch_layout(int code, bool aligned, dim3 grid, hipStream_t s, const KParams &kp) {
+  const dim3 block(NTHREADS);
+#define SOAP_LAUNCH(TA, TB)                                                                      \
+  do {                                                                                           \
+    if (aligned)                                                                                 \
+      hipLaunchKernelGGL((gemm_f32_split<TA, TB, V_ALIGNED, MODE, TAG, PERSIST>), grid, block, 0, \
+                         s, kp);                                                                 \
+    else                                                                                         \
+      hipLaunchKernelGGL((gemm_f32_split<TA, TB, V_ANY, MODE, TAG, PERSIST>), grid, block, 0, s,  \
+                         kp);                                                                    \
+  } while (0)
+  if constexpr (MODE == MODE_GENERAL && TAG == 0) {
+    switch (code) {
+      case 0: SOAP_LAUNCH(0, 0); break;
+      case 1: SOAP_LAUNCH(0, 1); break;
+      case 2: SOAP_LAUNCH(1, 0); break;
+      default: SOAP_LAUNCH(1, 1); break;
+    }
+  } else if constexpr (MODE == MODE_GENERAL) {   // the power products, by their own symbols
+    if (code != 2) return hipErrorInvalidValue;
+    SOAP_LAUNCH(1, 0);
+  } else if constexpr (MODE == MODE_SYRK) {      // X X^T and X^T X
+    if (code == 1) SOAP_LAUNCH(0, 1);
+    else if (code == 2) SOAP_LAUNCH(1, 0);
+    else return hipErrorInvalidValue;
+  } else {
+    if (code == 0) SOAP_LAUNCH(0, 0);
+    else if (code == 1) SOAP_LAUNCH(0, 1);
+    else return hipErrorInvalidValue;
+  }
+#undef SOAP_LAUNCH
+  return hipGetLastError();
+}
+
 template <int MODE>
-hipError_t dispatch(const GemmDesc &d, KParams &kp, hipStream_t s, bool vec_ok, bool vec_ok_kx) {
-  dim3 block(NTHREADS);
+hipError_t dispatch(const GemmDesc &d, KParams &kp, hipStream_t s, bool aligned) {
   const int S = (MODE == MODE_GENERAL && d.splitk > 1 && d.part) ? d.splitk : 1;
   // A cap counts every workgroup (split slices and batch included); the
   // tile dimension stays a multiple of 8 for XCD locality.
@@ -649,80 +671,18 @@ hipError_t dispatch(const GemmDesc &d, KParams &kp, hipStream_t s, bool vec_ok, 
                       (int64_t)kp.ntiles * per_tile > d.max_wg;
   const int wgs = capped ? (int)std::max<int64_t>(8, (d.max_wg / per_tile) & ~int64_t(7)) : kp.ntiles;
   dim3 grid(std::min(wgs, kp.ntiles), S, (unsigned)d.batch);
-#define SOAP_LAUNCH(TA, TB, VEC, TAG) \
-  hipLaunchKernelGGL((gemm_f32_mfma<TA, TB, VEC, MODE, TAG, 1>), grid, block, 0, s, kp)
   const int code = d.trans_a * 2 + d.trans_b;
-  if (MODE == MODE_SYRK && capped) {
-    // the two layouts of the factor products: X X^T (0, 1) and X^T X (1, 0)
-#define SOAP_LAUNCH_SP(TA, TB, VEC) \
-  hipLaunchKernelGGL((gemm_f32_mfma<TA, TB, VEC, MODE_SYRK, 0, 1, true>), grid, block, 0, s, kp)
-    if (code == 1) { if (vec_ok) SOAP_LAUNCH_SP(0, 1, 4); else SOAP_LAUNCH_SP(0, 1, 1); }
-    else if (code == 2) { if (vec_ok) SOAP_LAUNCH_SP(1, 0, 4); else SOAP_LAUNCH_SP(1, 0, 1); }
-    else return hipErrorInvalidValue;
-#undef SOAP_LAUNCH_SP
-  } else if (capped) {
-#define SOAP_LAUNCH_P(TA, TB, VEC, MINB) \
-  hipLaunchKernelGGL((gemm_f32_mfma<TA, TB, VEC, MODE_GENERAL, 0, MINB, true>), grid, block, 0, s, kp)
-    const bool shortk = kp.kslice <= SHORT_K;
-    switch (code * 4 + ((shortk ? vec_ok_kx : vec_ok) ? 2 : 0) + (shortk ? 1 : 0)) {
-      case 0: SOAP_LAUNCH_P(0, 0, 1, 1); break;
-      case 1: SOAP_LAUNCH_P(0, 0, 1, 3); break;
-      case 2: SOAP_LAUNCH_P(0, 0, 4, 1); break;
-      case 3: SOAP_LAUNCH_P(0, 0, 4, 3); break;
-      case 4: SOAP_LAUNCH_P(0, 1, 1, 1); break;
-      case 5: SOAP_LAUNCH_P(0, 1, 1, 3); break;
-      case 6: SOAP_LAUNCH_P(0, 1, 4, 1); break;
-      case 7: SOAP_LAUNCH_P(0, 1, 4, 3); break;
-      case 8: SOAP_LAUNCH_P(1, 0, 1, 1); break;
-      case 9: SOAP_LAUNCH_P(1, 0, 1, 3); break;
-      case 10: SOAP_LAUNCH_P(1, 0, 4, 1); break;
-      case 11: SOAP_LAUNCH_P(1, 0, 4, 3); break;
-      case 12: SOAP_LAUNCH_P(1, 1, 1, 1); break;
-      case 13: SOAP_LAUNCH_P(1, 1, 1, 3); break;
-      case 14: SOAP_LAUNCH_P(1, 1, 4, 1); break;
-      default: SOAP_LAUNCH_P(1, 1, 4, 3); break;
-    }
-#undef SOAP_LAUNCH_P
-  } else if (MODE == MODE_GENERAL && d.tag != 0 && code == 2) {
-    // the power products (transposed-A layout) under their own symbols
-    if (d.tag == 1) { if (vec_ok) SOAP_LAUNCH(1, 0, 4, 1); else SOAP_LAUNCH(1, 0, 1, 1); }
-    else { if (vec_ok) SOAP_LAUNCH(1, 0, 4, 2); else SOAP_LAUNCH(1, 0, 1, 2); }
-  } else if (MODE == MODE_GENERAL && kp.kslice <= SHORT_K) {
-#define SOAP_LAUNCH_RANK(TA, TB, VEC) \
-  hipLaunchKernelGGL((gemm_f32_mfma<TA, TB, VEC, MODE_GENERAL, 0, 3>), grid, block, 0, s, kp)
-    if (vec_ok_kx) {
-      switch (code) {
-        case 0: SOAP_LAUNCH_RANK(0, 0, 4); break;
-        case 1: SOAP_LAUNCH_RANK(0, 1, 4); break;
-        case 2: SOAP_LAUNCH_RANK(1, 0, 4); break;
-        default: SOAP_LAUNCH_RANK(1, 1, 4); break;
-      }
-    } else {
-      switch (code) {
-        case 0: SOAP_LAUNCH_RANK(0, 0, 1); break;
-        case 1: SOAP_LAUNCH_RANK(0, 1, 1); break;
-        case 2: SOAP_LAUNCH_RANK(1, 0, 1); break;
-        default: SOAP_LAUNCH_RANK(1, 1, 1); break;
-      }
-    }
-#undef SOAP_LAUNCH_RANK
-  } else if (vec_ok) {
-    switch (code) {
-      case 0: SOAP_LAUNCH(0, 0, 4, 0); break;
-      case 1: SOAP_LAUNCH(0, 1, 4, 0); break;
-      case 2: SOAP_LAUNCH(1, 0, 4, 0); break;
-      default: SOAP_LAUNCH(1, 1, 4, 0); break;
-    }
+  hipError_t err;
+  if constexpr (MODE != MODE_ADAM) {
+    if (capped) err = launch_layout<MODE, 0, true>(code, aligned, grid, s, kp);
+    else if (MODE == MODE_GENERAL && d.tag == 1 && code == 2)
+      err = launch_layout<MODE_GENERAL, 1, false>(code, aligned, grid, s, kp);
+    else if (MODE == MODE_GENERAL && d.tag == 2 && code == 2)
+      err = launch_layout<MODE_GENERAL, 2, false>(code, aligned, grid, s, kp);
+    else err = launch_layout<MODE, 0, false>(code, aligned, grid, s, kp);
   } else {
-    switch (code) {
-      case 0: SOAP_LAUNCH(0, 0, 1, 0); break;
-      case 1: SOAP_LAUNCH(0, 1, 1, 0); break;
-      case 2: SOAP_LAUNCH(1, 0, 1, 0); break;
-      default: SOAP_LAUNCH(1, 1, 1, 0); break;
-    }
+    err = launch_layout<MODE, 0, false>(code, aligned, grid, s, kp);
   }
-#undef SOAP_LAUNCH
-  hipError_t err = hipGetLastError();
   if (err != hipSuccess || S == 1 || d.partials_only) return err;
   int64_t mn = d.M * d.N;
   unsigned gx = (unsigned)std::min<int64_t>((mn + 255) / 256, 2048);
@@ -753,27 +713,20 @@ KParams make_params(const GemmDesc &d) {
   return kp;
 }
 
-// Vector loads: a k-contiguous operand uses 16-byte loads along k (k extent,
-// leading dimension, batch stride multiples of 4 floats, 16-byte aligned
-// base); an x-contiguous operand uses 8-byte loads along x (even x extent,
-// leading dimension and batch stride, 8-byte aligned base).
-
+// V_ALIGNED's preconditions: a k-contiguous operand is read 16 bytes at a time
+// along k (k extent, leading dimension, batch stride multiples of 4 floats,
+// 16-byte aligned base); an x-contiguous operand 8 bytes along x (even x
+// extent, leading dimension and batch stride, 8-byte aligned base).
 bool aligned8(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 7u) == 0; }
 
-// The vector path's preconditions; kx: the rank-k kernel, whose x-contiguous
-// operands are read 16 bytes at a time along x.
-bool vec_ok_for(const GemmDesc &d, bool kx) {
-  bool ok = true;
+bool aligned_loads(const GemmDesc &d) {
+  bool ok = d.K > 0;
   if (d.trans_a == 0)
     ok = ok && d.K % 4 == 0 && d.lda % 4 == 0 && d.sA % 4 == 0 && aligned16(d.A);
-  else if (kx)
-    ok = ok && d.M % 4 == 0 && d.lda % 4 == 0 && d.sA % 4 == 0 && aligned16(d.A);
   else
     ok = ok && d.M % 2 == 0 && d.lda % 2 == 0 && d.sA % 2 == 0 && aligned8(d.A);
   if (d.trans_b == 1)
     ok = ok && d.K % 4 == 0 && d.ldb % 4 == 0 && d.sB % 4 == 0 && aligned16(d.B);
-  else if (kx)
-    ok = ok && d.N % 4 == 0 && d.ldb % 4 == 0 && d.sB % 4 == 0 && aligned16(d.B);
   else
     ok = ok && d.N % 2 == 0 && d.ldb % 2 == 0 && d.sB % 2 == 0 && aligned8(d.B);
   return ok;
@@ -795,14 +748,14 @@ int choose_splitk(int64_t M, int64_t N, int64_t K, int64_t batch, int max_split)
 hipError_t launch_gemm(const GemmDesc &d, hipStream_t s) {
   if (d.M <= 0 || d.N <= 0 || d.batch <= 0) return hipSuccess;
   KParams kp = make_params(d);
-  return dispatch<MODE_GENERAL>(d, kp, s, vec_ok_for(d, false), vec_ok_for(d, true));
+  return dispatch<MODE_GENERAL>(d, kp, s, aligned_loads(d));
 }
 
 hipError_t launch_syrk_ema(const GemmDesc &d, hipStream_t s) {
   if (d.M <= 0 || d.batch <= 0) return hipSuccess;
   KParams kp = make_params(d);
   kp.ntiles = kp.tiles_m * (kp.tiles_m + 1) / 2;
-  return dispatch<MODE_SYRK>(d, kp, s, vec_ok_for(d, false), vec_ok_for(d, true));
+  return dispatch<MODE_SYRK>(d, kp, s, aligned_loads(d));
 }
 
 hipError_t launch_gemm_adam(const GemmDesc &d, const AdamEpi &e, hipStream_t s) {
@@ -812,7 +765,7 @@ hipError_t launch_gemm_adam(const GemmDesc &d, const AdamEpi &e, hipStream_t s) 
   kp.V = e.V;
   kp.Nout = e.Nout;
   kp.b2 = e.b2; kp.c1 = e.c1; kp.c2 = e.c2; kp.eps = e.eps;
-  return dispatch<MODE_ADAM>(d, kp, s, vec_ok_for(d, false), vec_ok_for(d, true));
+  return dispatch<MODE_ADAM>(d, kp, s, aligned_loads(d));
 }
 
 }  // namespace soap
