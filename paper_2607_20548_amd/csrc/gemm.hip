@@ -22,8 +22,8 @@
 // products (a large library product in bfloat16 runs at 1.37 PFLOP/s).
 //
 // Tiling: a 256-thread workgroup (4 wave64s in a 2 x 2 arrangement) computes a
-// 128 x 128 tile of C; each wave owns a 64 x 64 sub-tile held as 2 x 2 32x32
-// accumulators.  K advances in slabs of 32; the global loads of the next slab
+// 128 x 128 tile of C (64 x 64 for products with few tiles); each wave owns a
+// 64 x 64 sub-tile held as 2 x 2 32x32 accumulators.  K advances in slabs of 32; the global loads of the next slab
 // are in flight while a slab is multiplied.
 //
 // Epilogue: the tile goes through LDS (free after the K loop) so that C is read
@@ -43,21 +43,28 @@ typedef float v2f __attribute__((ext_vector_type(2)));
 typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 
-constexpr int BM = 128;
-constexpr int BN = 128;
+constexpr int BIG = 128;      // tile rows and columns
+constexpr int SMALL = 64;     // of products whose 128-tiles leave compute units idle
 constexpr int BK = 32;
 constexpr int NTHREADS = 256;
 constexpr int GROUP_M = 8;
 
-// LDS image of one operand slab (128 x-rows, 32 k): three bfloat16 planes; in
+// LDS image of one operand slab (BT x-rows, 32 k): three bfloat16 planes; in
 // a plane the 16-byte unit (x, g) holds k = 8 g .. 8 g + 7 of row x, at
-// g * LDS_G + (x / 2) * 16 + (x % 2) * LDS_ODD.  A fragment read (one g, 32
+// g * GROUP + (x / 2) * 16 + (x % 2) * ODD.  A fragment read (one g, 32
 // consecutive x) then covers all banks every eight lanes, and so do the
-// writes of both loaders (x pairs of one g; four g of two rows).
-constexpr int LDS_ODD = 64 * 16 + 64;
-constexpr int LDS_G = 2 * LDS_ODD + 16;
-constexpr int LDS_PLANE = 4 * LDS_G;
-constexpr int LDS_OPERAND = 3 * LDS_PLANE;
+// writes of both loaders (x pairs or consecutive x of one g; four g of two
+// rows).
+template <int BT>
+struct Lds {
+  static constexpr int ODD = BT / 2 * 16 + 64;
+  static constexpr int GROUP = 2 * ODD + 16;
+  static constexpr int PLANE = 4 * GROUP;
+  static constexpr int OPERAND = 3 * PLANE;
+  static __device__ __forceinline__ int unit(int x, int g) {
+    return g * GROUP + (x >> 1) * 16 + (x & 1) * ODD;
+  }
+};
 
 // Sums below this (2^-90, as bits) are taken again in fp32.
 constexpr uint32_t EXACT_BELOW = (127u - 90u) << 23;
@@ -87,10 +94,6 @@ struct KParams {
   int64_t sSkip;
 };
 
-__device__ __forceinline__ int lds_unit(int x, int g) {
-  return g * LDS_G + (x >> 1) * 16 + (x & 1) * LDS_ODD;
-}
-
 struct f4u { float x, y, z, w; };   // 4-byte aligned
 struct f2u { float x, y; };
 
@@ -110,39 +113,42 @@ __device__ __forceinline__ void split2(float x0, float x1, uint32_t &hi, uint32_
 }
 
 // Splits eight consecutive k of row x and writes them as unit (x, g).
+template <int BT>
 __device__ __forceinline__ void store_unit(char *lds, int x, int g, const float (&v)[8]) {
   uint4 h, m, l;
   split2(v[0], v[1], h.x, m.x, l.x);
   split2(v[2], v[3], h.y, m.y, l.y);
   split2(v[4], v[5], h.z, m.z, l.z);
   split2(v[6], v[7], h.w, m.w, l.w);
-  char *dst = lds + lds_unit(x, g);
+  char *dst = lds + Lds<BT>::unit(x, g);
   *reinterpret_cast<uint4 *>(dst) = h;
-  *reinterpret_cast<uint4 *>(dst + LDS_PLANE) = m;
-  *reinterpret_cast<uint4 *>(dst + 2 * LDS_PLANE) = l;
+  *reinterpret_cast<uint4 *>(dst + Lds<BT>::PLANE) = m;
+  *reinterpret_cast<uint4 *>(dst + 2 * Lds<BT>::PLANE) = l;
 }
 
-// One operand slab of 128 x-rows by BK k-values: 16 values per thread.
+// One operand slab of BT x-rows by BK k-values: RPT rows of 8 values per thread.
 //   KCONTIG = true : global element (x, k) at base[x*ld + k]; a thread holds
-//     k-octet tid & 3 of rows tid >> 2 and 64 + (tid >> 2)
+//     k-octet tid & 3 of rows tid >> 2 and (BT = 128) 64 + (tid >> 2)
 //   KCONTIG = false: global element (x, k) at base[k*ld + x]; a thread holds
-//     the k-octet of its wave (tid >> 6) for rows 2 lane, 2 lane + 1
+//     the k-octet of its wave (tid >> 6) for rows 2 lane, 2 lane + 1 (BT =
+//     128) or row lane (BT = 64)
 // Every load is issued unconditionally at an address clamped into the
 // matrix, so nothing consumes a loaded register before store(): rows x >= X
 // only reach output rows or columns that are never written, and k-values
 // past the end of K are zeroed by store().  V_ALIGNED needs K % 4 == 0 (and
 // the row starts 16-byte aligned) for k-contiguous operands and an even X
 // (8-byte aligned rows) for x-contiguous ones.
-template <bool KCONTIG, int LOADS>
+template <int BT, bool KCONTIG, int LOADS>
 struct SlabLoader {
-  float r[2][8];
+  static constexpr int RPT = BT / 64;
+  float r[RPT][8];
 
   __device__ __forceinline__ void load(const float *__restrict__ base, int64_t ld, int x0,
                                        int k0, int X, int K, int tid) {
     if constexpr (KCONTIG) {
       const int k = k0 + 8 * (tid & 3);
 #pragma unroll
-      for (int s = 0; s < 2; ++s) {
+      for (int s = 0; s < RPT; ++s) {
         const float *row = base + (int64_t)min(x0 + (tid >> 2) + 64 * s, X - 1) * ld;
         if (LOADS == V_ALIGNED) {
 #pragma unroll
@@ -165,8 +171,8 @@ struct SlabLoader {
       // k is uniform within a wave: the row address is formed on the scalar
       // unit and each lane adds its column offset.
       const int k = k0 + 8 * __builtin_amdgcn_readfirstlane(tid >> 6);
-      const int x = x0 + 2 * (tid & 63);
-      if (LOADS == V_ALIGNED || X > 1) {
+      if (RPT == 2 && (LOADS == V_ALIGNED || X > 1)) {
+        const int x = x0 + 2 * (tid & 63);
         const unsigned xc = (unsigned)min(x, X - 2);
         // an odd X: the last row is the second of the clamped pair
         const bool odd = LOADS == V_ANY && x == X - 1;
@@ -182,11 +188,13 @@ struct SlabLoader {
             vx = v.x; vy = v.y;
           }
           r[0][e] = odd ? vy : vx;
-          r[1][e] = vy;
+          r[RPT - 1][e] = vy;
         }
-      } else {
+      } else {   // one row per thread (or a single row in all)
+        const unsigned xc = (unsigned)min(x0 + (tid & 63), X - 1);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) r[0][e] = r[1][e] = base[(int64_t)min(k + e, K - 1) * ld];
+        for (int e = 0; e < 8; ++e)
+          r[0][e] = r[RPT - 1][e] = (base + (int64_t)min(k + e, K - 1) * ld)[xc];
       }
     }
   }
@@ -198,11 +206,13 @@ struct SlabLoader {
     if (kvalid < BK) {
 #pragma unroll
       for (int e = 0; e < 8; ++e)
-        if (8 * g + e >= kvalid) r[0][e] = r[1][e] = 0.f;
+#pragma unroll
+        for (int s = 0; s < RPT; ++s)
+          if (8 * g + e >= kvalid) r[s][e] = 0.f;
     }
 #pragma unroll
-    for (int s = 0; s < 2; ++s)
-      store_unit(lds, KCONTIG ? (tid >> 2) + 64 * s : 2 * (tid & 63) + s, g, r[s]);
+    for (int s = 0; s < RPT; ++s)
+      store_unit<BT>(lds, KCONTIG ? (tid >> 2) + 64 * s : RPT * (tid & 63) + s, g, r[s]);
   }
 };
 
@@ -240,9 +250,19 @@ __device__ __forceinline__ void tile_coords(const KParams &p, int t, int &tm, in
 // blocks' slab sums, the slab in flight and the fragments of a block), whose
 // loads, splits and matrix instructions overlap one another; bounded to
 // three, the slab sums spill (180 -> 89 TFLOP/s).
-template <int TA, int TB, int LOADS, int MODE, int TAG, bool PERSIST = false>
-__global__ __launch_bounds__(NTHREADS, 2) void gemm_f32_split(KParams p) {
-  __shared__ __attribute__((aligned(16))) char lds_raw[2 * LDS_OPERAND];
+//
+// BT = 64 is for products with few tiles (four waves of one 32 x 32 block
+// each): four times the workgroups, a quarter of the work in each, and three
+// slabs in flight, since such products wait for memory.
+template <int BT, int TA, int TB, int LOADS, int MODE, int TAG, bool PERSIST = false>
+__global__ __launch_bounds__(NTHREADS, BT == BIG ? 2 : 3) void gemm_f32_split(KParams p) {
+  using LD = Lds<BT>;
+  constexpr int WT = BT / 2;        // a wave's tile
+  constexpr int NBLK = WT / 32;     // its 32 x 32 blocks each way
+  constexpr int AHEAD = BT == BIG ? 1 : 3;
+  constexpr int SLD = BT + 4;       // LDS row of the epilogue's staging (WT rows)
+  constexpr int LDS_BYTES = 2 * LD::OPERAND > WT * SLD * 4 ? 2 * LD::OPERAND : WT * SLD * 4;
+  __shared__ __attribute__((aligned(16))) char lds_raw[LDS_BYTES];
   float *const lds = reinterpret_cast<float *>(lds_raw);
   if (p.skip && p.skip[(int64_t)blockIdx.z * p.sSkip] != 0u) return;
 
@@ -254,7 +274,7 @@ __global__ __launch_bounds__(NTHREADS, 2) void gemm_f32_split(KParams p) {
   const int64_t bz = blockIdx.z;
   const float *A = p.A + bz * p.sA;
   const float *B = p.B + bz * p.sB;
-  const int m0 = tm * BM, n0 = tn * BN;
+  const int m0 = tm * BT, n0 = tn * BT;
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
@@ -262,34 +282,40 @@ __global__ __launch_bounds__(NTHREADS, 2) void gemm_f32_split(KParams p) {
 
   // op(A) rows are x = i: k-contiguous when TA == 0.  op(B) columns are x = j:
   // k-contiguous when TB == 1.
-  SlabLoader<TA == 0, LOADS> la;
-  SlabLoader<TB == 1, LOADS> lb;
+  SlabLoader<BT, TA == 0, LOADS> la[AHEAD];
+  SlabLoader<BT, TB == 1, LOADS> lb[AHEAD];
 
-  v16f acc[2][2];
+  v16f acc[NBLK][NBLK];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < NBLK; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < NBLK; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-  char *const sa = lds_raw, *const sb = lds_raw + LDS_OPERAND;
+  char *const sa = lds_raw, *const sb = lds_raw + LD::OPERAND;
   const int kbeg = blockIdx.y * p.kslice;
   const int kend = min(p.K, kbeg + p.kslice);
   const int nk = (kend - kbeg + BK - 1) / BK;
-  if (nk > 0) {
-    la.load(A, p.lda, m0, kbeg, p.M, kend, tid);
-    lb.load(B, p.ldb, n0, kbeg, p.N, kend, tid);
-  }
-  for (int kt = 0; kt < nk; ++kt) {
+#pragma unroll
+  for (int u = 0; u < AHEAD; ++u)
+    if (u < nk) {
+      la[u].load(A, p.lda, m0, kbeg + u * BK, p.M, kend, tid);
+      lb[u].load(B, p.ldb, n0, kbeg + u * BK, p.N, kend, tid);
+    }
+  for (int kt0 = 0; kt0 < nk; kt0 += AHEAD) {
+#pragma unroll
+  for (int u = 0; u < AHEAD; ++u) {
+    const int kt = kt0 + u;
+    if (AHEAD > 1 && kt >= nk) break;
     const int k0 = kbeg + kt * BK;
     const int kvalid = min(BK, kend - k0);
-    la.store(sa, tid, kvalid);
-    lb.store(sb, tid, kvalid);
+    la[u].store(sa, tid, kvalid);
+    lb[u].store(sb, tid, kvalid);
     __syncthreads();
-    if (kt + 1 < nk) {
-      la.load(A, p.lda, m0, k0 + BK, p.M, kend, tid);
-      lb.load(B, p.ldb, n0, k0 + BK, p.N, kend, tid);
+    if (kt + AHEAD < nk) {
+      la[u].load(A, p.lda, m0, k0 + AHEAD * BK, p.M, kend, tid);
+      lb[u].load(B, p.ldb, n0, k0 + AHEAD * BK, p.N, kend, tid);
     }
     // block by block: the slab's sums from zero, then into the accumulators
     v8bf fa[2][3], fb[2][3];
@@ -299,7 +325,7 @@ __global__ __launch_bounds__(NTHREADS, 2) void gemm_f32_split(KParams p) {
 #pragma unroll
         for (int pl = 0; pl < 3; ++pl)
           f[q][pl] = __builtin_bit_cast(v8bf, *reinterpret_cast<const uint4 *>(
-              base + pl * LDS_PLANE + lds_unit(x, 2 * q + h)));
+              base + pl * LD::PLANE + LD::unit(x, 2 * q + h)));
     };
     auto block = [&](v16f &c) {
       v16f t;
@@ -307,25 +333,28 @@ __global__ __launch_bounds__(NTHREADS, 2) void gemm_f32_split(KParams p) {
       for (int r = 0; r < 16; ++r) t[r] = 0.f;
       // the six products above 2^-27 of the largest, the small ones first
 #pragma unroll
-      for (int u = 0; u < 6; ++u) {
+      for (int v = 0; v < 6; ++v) {
         constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};
 #pragma unroll
         for (int q = 0; q < 2; ++q)
-          t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[q][pa[u]], fb[q][pb[u]], t, 0, 0, 0);
+          t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[q][pa[v]], fb[q][pb[v]], t, 0, 0, 0);
       }
 #pragma unroll
       for (int r = 0; r < 16; ++r) c[r] += t[r];
     };
-    frag(sa, wm * 64 + xl, fa);
-    frag(sb, wn * 64 + xl, fb);
+    frag(sa, wm * WT + xl, fa);
+    frag(sb, wn * WT + xl, fb);
     block(acc[0][0]);
-    frag(sb, wn * 64 + 32 + xl, fb);
-    block(acc[0][1]);
-    frag(sa, wm * 64 + 32 + xl, fa);
-    block(acc[1][1]);
-    frag(sb, wn * 64 + xl, fb);
-    block(acc[1][0]);
+    if constexpr (NBLK == 2) {
+      frag(sb, wn * WT + 32 + xl, fb);
+      block(acc[0][1]);
+      frag(sa, wm * WT + 32 + xl, fa);
+      block(acc[1][1]);
+      frag(sb, wn * WT + xl, fb);
+      block(acc[1][0]);
+    }
     __syncthreads();
+  }
   }
 
   // A wave whose sums hold an infinity or a NaN (an infinite operand times a
@@ -336,36 +365,36 @@ __global__ __launch_bounds__(NTHREADS, 2) void gemm_f32_split(KParams p) {
   {
     uint32_t mx = 0u;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < NBLK; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
+      for (int j = 0; j < NBLK; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) mx = max(mx, __float_as_uint(acc[i][j][r]) & 0x7fffffffu);
     const bool big = __any(mx >= 0x7f800000u);
     const bool tiny = __any(mx != 0u) && !__any(mx >= EXACT_BELOW);
     if (big || tiny) {
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < NBLK; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < NBLK; ++j)
 #pragma unroll
           for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 #pragma unroll 1
       for (int k = kbeg; k < kend; k += 2) {
         const int kk = min(k + h, kend - 1);
         const float live = (k + h < kend) ? 1.f : 0.f;
-        float ea[2], eb[2];
+        float ea[NBLK], eb[NBLK];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          const float va = operand_at<TA == 0>(A, p.lda, m0 + wm * 64 + 32 * i + xl, kk, p.M);
-          const float vb = operand_at<TB == 1>(B, p.ldb, n0 + wn * 64 + 32 * i + xl, kk, p.N);
+        for (int i = 0; i < NBLK; ++i) {
+          const float va = operand_at<TA == 0>(A, p.lda, m0 + wm * WT + 32 * i + xl, kk, p.M);
+          const float vb = operand_at<TB == 1>(B, p.ldb, n0 + wn * WT + 32 * i + xl, kk, p.N);
           ea[i] = live != 0.f ? va : 0.f;
           eb[i] = live != 0.f ? vb : 0.f;
         }
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < NBLK; ++i)
 #pragma unroll
-          for (int j = 0; j < 2; ++j)
+          for (int j = 0; j < NBLK; ++j)
             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(ea[i], eb[j], acc[i][j], 0, 0, 0);
       }
     }
@@ -378,15 +407,16 @@ __global__ __launch_bounds__(NTHREADS, 2) void gemm_f32_split(KParams p) {
   float *V = (MODE == MODE_ADAM) ? p.V + bz * p.sC : nullptr;
   float *Nout = (MODE == MODE_ADAM) ? p.Nout + bz * p.sC : nullptr;
   bool staged = false;
+  constexpr int NQ = WT * BT / 4 / NTHREADS;   // float4 of a half per thread
+  constexpr int QG = NQ < 4 ? NQ : 4;
   if constexpr (MODE == MODE_SYRK) {
    if ((reinterpret_cast<uintptr_t>(C) & 15u) == 0 && (p.ldc & 3) == 0) {
     staged = true;
-    // One triangle, mirrored, through LDS in two halves of 64 rows: the
+    // One triangle, mirrored, through LDS in two halves of WT rows: the
     // lower part (row >= col) is written as beta C + alpha acc with 16-byte
     // reads and writes, the final values go back to LDS, and the mirror is
     // written from the transposed half, again 16 bytes per lane (scattered
     // 4-byte mirror stores, and a read of C after each store, otherwise).
-    constexpr int SLD = BN + 4;
     float *stage = lds;
     const bool read_back = p.beta != 0.f;
 #pragma unroll
@@ -394,23 +424,23 @@ __global__ __launch_bounds__(NTHREADS, 2) void gemm_f32_split(KParams p) {
       __syncthreads();
       if (wm == half) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < NBLK; ++i)
 #pragma unroll
-          for (int j = 0; j < 2; ++j)
+          for (int j = 0; j < NBLK; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r)
-              stage[(i * 32 + 8 * (r >> 2) + 4 * h + (r & 3)) * SLD + wn * 64 + j * 32 + xl] =
+              stage[(i * 32 + 8 * (r >> 2) + 4 * h + (r & 3)) * SLD + wn * WT + j * 32 + xl] =
                   acc[i][j][r];
       }
       __syncthreads();
 #pragma unroll
-      for (int g4 = 0; g4 < 2; ++g4) {   // two groups of 4 (registers of the main loop)
-        float4 cv[4];
+      for (int g4 = 0; g4 < NQ / QG; ++g4) {   // groups of 4 (registers of the main loop)
+        float4 cv[QG];
 #pragma unroll
-        for (int qq = 0; qq < 4; ++qq) {
-          const int q = 4 * g4 + qq;
-          const int e = tid + NTHREADS * q, lrow = e >> 5, c4 = (e & 31) * 4;
-          const int row = m0 + half * 64 + lrow, col = n0 + c4;
+        for (int qq = 0; qq < QG; ++qq) {
+          const int q = QG * g4 + qq;
+          const int e = tid + NTHREADS * q, lrow = e / (BT / 4), c4 = (e % (BT / 4)) * 4;
+          const int row = m0 + half * WT + lrow, col = n0 + c4;
           cv[qq] = make_float4(0.f, 0.f, 0.f, 0.f);
           // only the lower triangle is read (a float4 with col <= row holds at
           // least one element of it; the others are masked)
@@ -428,10 +458,10 @@ __global__ __launch_bounds__(NTHREADS, 2) void gemm_f32_split(KParams p) {
         }
         asm volatile("" ::: "memory");
 #pragma unroll
-        for (int qq = 0; qq < 4; ++qq) {
-          const int q = 4 * g4 + qq;
-          const int e = tid + NTHREADS * q, lrow = e >> 5, c4 = (e & 31) * 4;
-          const int row = m0 + half * 64 + lrow, col = n0 + c4;
+        for (int qq = 0; qq < QG; ++qq) {
+          const int q = QG * g4 + qq;
+          const int e = tid + NTHREADS * q, lrow = e / (BT / 4), c4 = (e % (BT / 4)) * 4;
+          const int row = m0 + half * WT + lrow, col = n0 + c4;
           float *sp = stage + lrow * SLD + c4;
           const float4 a = *reinterpret_cast<const float4 *>(sp);
           float4 v;
@@ -457,9 +487,9 @@ __global__ __launch_bounds__(NTHREADS, 2) void gemm_f32_split(KParams p) {
       // mirror: C[col][row] for row > col; thread -> (lc = output row within
       // the tile's columns, 4 consecutive rows of this half as output columns)
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const int e = tid + NTHREADS * q, lc = e >> 4, r4 = (e & 15) * 4;
-        const int orow = n0 + lc, ocol = m0 + half * 64 + r4;   // C[orow][ocol] = value(ocol, orow)
+      for (int q = 0; q < NQ; ++q) {
+        const int e = tid + NTHREADS * q, lc = e / (WT / 4), r4 = (e % (WT / 4)) * 4;
+        const int orow = n0 + lc, ocol = m0 + half * WT + r4;   // C[orow][ocol] = value(ocol, orow)
         if (orow >= p.N || ocol >= p.M) continue;
         float4 v;
         v.x = stage[(r4 + 0) * SLD + lc];
@@ -485,10 +515,9 @@ __global__ __launch_bounds__(NTHREADS, 2) void gemm_f32_split(KParams p) {
    if (!P && (reinterpret_cast<uintptr_t>(C) & 15u) == 0 && (p.ldc & 3) == 0) {
     staged = true;
     // Rank-k updates are bound by their pass over C, so the tile goes
-    // through LDS (free after the K loop) in two halves of 64 rows and C is
+    // through LDS (free after the K loop) in two halves of WT rows and C is
     // read and written 16 bytes per lane, all reads of a thread before its
     // stores.
-    constexpr int SLD = BN + 4;   // padded LDS row (64 rows x 132 floats fit the 40 KB)
     float *stage = lds;
     const bool read_back = p.beta != 0.f;
 #pragma unroll
@@ -496,20 +525,20 @@ __global__ __launch_bounds__(NTHREADS, 2) void gemm_f32_split(KParams p) {
       __syncthreads();
       if (wm == half) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < NBLK; ++i)
 #pragma unroll
-          for (int j = 0; j < 2; ++j)
+          for (int j = 0; j < NBLK; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r)
-              stage[(i * 32 + 8 * (r >> 2) + 4 * h + (r & 3)) * SLD + wn * 64 + j * 32 + xl] =
+              stage[(i * 32 + 8 * (r >> 2) + 4 * h + (r & 3)) * SLD + wn * WT + j * 32 + xl] =
                   acc[i][j][r];
       }
       __syncthreads();
-      float4 cv[8];
+      float4 cv[NQ];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const int e = tid + NTHREADS * q, lrow = e >> 5, c4 = (e & 31) * 4;
-        const int row = m0 + half * 64 + lrow, col = n0 + c4;
+      for (int q = 0; q < NQ; ++q) {
+        const int e = tid + NTHREADS * q, lrow = e / (BT / 4), c4 = (e % (BT / 4)) * 4;
+        const int row = m0 + half * WT + lrow, col = n0 + c4;
         cv[q] = make_float4(0.f, 0.f, 0.f, 0.f);
         if (read_back && row < p.M) {
           const float *src = C + (int64_t)row * p.ldc + col;
@@ -523,9 +552,9 @@ __global__ __launch_bounds__(NTHREADS, 2) void gemm_f32_split(KParams p) {
         }
       }
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const int e = tid + NTHREADS * q, lrow = e >> 5, c4 = (e & 31) * 4;
-        const int row = m0 + half * 64 + lrow, col = n0 + c4;
+      for (int q = 0; q < NQ; ++q) {
+        const int e = tid + NTHREADS * q, lrow = e / (BT / 4), c4 = (e % (BT / 4)) * 4;
+        const int row = m0 + half * WT + lrow, col = n0 + c4;
         if (row >= p.M) continue;
         const float4 a = *reinterpret_cast<const float4 *>(stage + lrow * SLD + c4);
         float4 v;
@@ -551,10 +580,10 @@ __global__ __launch_bounds__(NTHREADS, 2) void gemm_f32_split(KParams p) {
     // done
   } else {
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < NBLK; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int col = n0 + wn * 64 + j * 32 + xl;
+      for (int j = 0; j < NBLK; ++j) {
+        const int col = n0 + wn * WT + j * 32 + xl;
         // C = alpha acc + beta C: the 16 values of C of this block are read
         // before its stores (one memory latency per block instead of one per
         // element); the empty asm keeps the compiler from hoisting the reads
@@ -564,14 +593,14 @@ __global__ __launch_bounds__(NTHREADS, 2) void gemm_f32_split(KParams p) {
         if (MODE == MODE_GENERAL && !P) {
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
-            const int row = m0 + wm * 64 + i * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
+            const int row = m0 + wm * WT + i * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
             cv[r] = (p.beta != 0.f && row < p.M && col < p.N) ? C[(int64_t)row * p.ldc + col] : 0.f;
           }
         }
         asm volatile("" ::: "memory");
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int row = m0 + wm * 64 + i * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
+          const int row = m0 + wm * WT + i * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
           if (row >= p.M || col >= p.N) continue;
           const int64_t off = (int64_t)row * p.ldc + col;
           if (MODE == MODE_GENERAL && P) {
@@ -626,16 +655,16 @@ __global__ __launch_bounds__(256) void splitk_reduce(const float *__restrict__ p
 
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-template <int MODE, int TAG, bool PERSIST>
+template <int BT, int MODE, int TAG, bool PERSIST>
 hipError_t launch_layout(int code, bool aligned, dim3 grid, hipStream_t s, const KParams &kp) {
   const dim3 block(NTHREADS);
 #define SOAP_LAUNCH(TA, TB)                                                                      \
   do {                                                                                           \
     if (aligned)                                                                                 \
-      hipLaunchKernelGGL((gemm_f32_split<TA, TB, V_ALIGNED, MODE, TAG, PERSIST>), grid, block, 0, \
+      hipLaunchKernelGGL((gemm_f32_split<BT, TA, TB, V_ALIGNED, MODE, TAG, PERSIST>), grid, block, 0, \
                          s, kp);                                                                 \
     else                                                                                         \
-      hipLaunchKernelGGL((gemm_f32_split<TA, TB, V_ANY, MODE, TAG, PERSIST>), grid, block, 0, s,  \
+      hipLaunchKernelGGL((gemm_f32_split<BT, TA, TB, V_ANY, MODE, TAG, PERSIST>), grid, block, 0, s,  \
                          kp);                                                                    \
   } while (0)
   if constexpr (MODE == MODE_GENERAL && TAG == 0) {
@@ -661,27 +690,48 @@ hipError_t launch_layout(int code, bool aligned, dim3 grid, hipStream_t s, const
   return hipGetLastError();
 }
 
+// Products of at most this many 128-tiles (split slices and batch included)
+// take 64-tiles: below it compute units stay idle with 128-tiles and each
+// tile's chain of slabs is what takes the time (128 x 128 x 128: 17 -> 8 us;
+// 517 x 517 x 1283, 25 tiles: 132 -> 49; 1536^3, 144 tiles: 112 -> 83; a
+// triangle of 136 tiles, K = 2048: 141 -> 92); from 256 tiles on the larger
+// tile's fewer bytes per flop win (2048^3: 151 us with 128-tiles, 163 with
+// 64-tiles; 3072 x 2048 x 2048, 384 tiles: 173 and 209).
+constexpr int64_t SMALL_MAX_TILES = 192;
+
+void set_tiles(KParams &kp, int bt, bool triangle) {
+  kp.tiles_m = (kp.M + bt - 1) / bt;
+  kp.tiles_n = (kp.N + bt - 1) / bt;
+  kp.ntiles = triangle ? kp.tiles_m * (kp.tiles_m + 1) / 2 : kp.tiles_m * kp.tiles_n;
+}
+
 template <int MODE>
 hipError_t dispatch(const GemmDesc &d, KParams &kp, hipStream_t s, bool aligned) {
+  hipError_t err;
   const int S = (MODE == MODE_GENERAL && d.splitk > 1 && d.part) ? d.splitk : 1;
   // A cap counts every workgroup (split slices and batch included); the
   // tile dimension stays a multiple of 8 for XCD locality.
   const int64_t per_tile = (int64_t)S * d.batch;
   const bool capped = (MODE == MODE_GENERAL || MODE == MODE_SYRK) && d.max_wg > 0 &&
                       (int64_t)kp.ntiles * per_tile > d.max_wg;
-  const int wgs = capped ? (int)std::max<int64_t>(8, (d.max_wg / per_tile) & ~int64_t(7)) : kp.ntiles;
-  dim3 grid(std::min(wgs, kp.ntiles), S, (unsigned)d.batch);
   const int code = d.trans_a * 2 + d.trans_b;
-  hipError_t err;
-  if constexpr (MODE != MODE_ADAM) {
-    if (capped) err = launch_layout<MODE, 0, true>(code, aligned, grid, s, kp);
-    else if (MODE == MODE_GENERAL && d.tag == 1 && code == 2)
-      err = launch_layout<MODE_GENERAL, 1, false>(code, aligned, grid, s, kp);
-    else if (MODE == MODE_GENERAL && d.tag == 2 && code == 2)
-      err = launch_layout<MODE_GENERAL, 2, false>(code, aligned, grid, s, kp);
-    else err = launch_layout<MODE, 0, false>(code, aligned, grid, s, kp);
+  if (kp.ntiles * per_tile <= SMALL_MAX_TILES && d.max_wg == 0) {
+    set_tiles(kp, SMALL, MODE == MODE_SYRK);
+    err = launch_layout<SMALL, MODE, 0, false>(code, aligned, dim3(kp.ntiles, S, (unsigned)d.batch),
+                                               s, kp);
   } else {
-    err = launch_layout<MODE, 0, false>(code, aligned, grid, s, kp);
+    const int wgs = capped ? (int)std::max<int64_t>(8, (d.max_wg / per_tile) & ~int64_t(7)) : kp.ntiles;
+    const dim3 grid(std::min(wgs, kp.ntiles), S, (unsigned)d.batch);
+    if constexpr (MODE != MODE_ADAM) {
+      if (capped) err = launch_layout<BIG, MODE, 0, true>(code, aligned, grid, s, kp);
+      else if (MODE == MODE_GENERAL && d.tag == 1 && code == 2)
+        err = launch_layout<BIG, MODE_GENERAL, 1, false>(code, aligned, grid, s, kp);
+      else if (MODE == MODE_GENERAL && d.tag == 2 && code == 2)
+        err = launch_layout<BIG, MODE_GENERAL, 2, false>(code, aligned, grid, s, kp);
+      else err = launch_layout<BIG, MODE, 0, false>(code, aligned, grid, s, kp);
+    } else {
+      err = launch_layout<BIG, MODE, 0, false>(code, aligned, grid, s, kp);
+    }
   }
   if (err != hipSuccess || S == 1 || d.partials_only) return err;
   int64_t mn = d.M * d.N;
@@ -691,16 +741,14 @@ hipError_t dispatch(const GemmDesc &d, KParams &kp, hipStream_t s, bool aligned)
   return hipGetLastError();
 }
 
-KParams make_params(const GemmDesc &d) {
+KParams make_params(const GemmDesc &d, bool triangle = false) {
   KParams kp{};
   kp.M = (int)d.M; kp.N = (int)d.N; kp.K = (int)d.K;
   kp.A = d.A; kp.lda = d.lda; kp.sA = d.sA;
   kp.B = d.B; kp.ldb = d.ldb; kp.sB = d.sB;
   kp.C = d.C; kp.ldc = d.ldc; kp.sC = d.sC;
   kp.alpha = d.alpha; kp.beta = d.beta;
-  kp.tiles_m = (int)((d.M + BM - 1) / BM);
-  kp.tiles_n = (int)((d.N + BN - 1) / BN);
-  kp.ntiles = kp.tiles_m * kp.tiles_n;
+  set_tiles(kp, BIG, triangle);
   kp.kslice = (int)d.K;
   kp.part = nullptr;
   kp.skip = d.skip;
@@ -735,7 +783,7 @@ bool aligned_loads(const GemmDesc &d) {
 }  // namespace
 
 int choose_splitk(int64_t M, int64_t N, int64_t K, int64_t batch, int max_split) {
-  const int64_t tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN) * batch;
+  const int64_t tiles = ((M + BIG - 1) / BIG) * ((N + BIG - 1) / BIG) * batch;
   if (tiles <= 0) return 1;   // an empty product: nothing to split
   int64_t s = (512 + tiles - 1) / tiles;
   const int64_t kcap = K / 512;     // keep at least 512 of K per slice
@@ -753,8 +801,7 @@ hipError_t launch_gemm(const GemmDesc &d, hipStream_t s) {
 
 hipError_t launch_syrk_ema(const GemmDesc &d, hipStream_t s) {
   if (d.M <= 0 || d.batch <= 0) return hipSuccess;
-  KParams kp = make_params(d);
-  kp.ntiles = kp.tiles_m * (kp.tiles_m + 1) / 2;
+  KParams kp = make_params(d, true);
   return dispatch<MODE_SYRK>(d, kp, s, aligned_loads(d));
 }
 

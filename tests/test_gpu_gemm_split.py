@@ -47,6 +47,8 @@ def operand(rows, cols, pad, shift, seed, scale=1.0):
     (1, 1, 1, 0, 0), (2, 3, 5, 1, 1), (127, 129, 31, 0, 0), (128, 128, 32, 0, 0),
     (129, 127, 33, 0, 3), (130, 2, 64, 2, 2), (1, 257, 65, 0, 0), (255, 1, 100, 3, 1),
     (132, 260, 96, 4, 0), (64, 512, 2049, 0, 0),
+    # more than 192 tiles of 128: the large tile
+    (1801, 2051, 65, 1, 1), (2050, 1796, 96, 0, 0), (1920, 1665, 33, 0, 2),
 ])
 def test_layouts_edges_and_alignment(soap, ta, tb, M, N, K, pad, shift):
     import torch
