@@ -254,8 +254,7 @@ size_t soap_workspace_update_offset(int64_t batch, int64_t m, int64_t n);
  * bounded waits gives up at once and every kernel still exits normally: the
  * give-up path above, on demand.  mask = 0 restores normal operation.  Only
  * QRs that take the resident block path are affected (matrices whose
- * factorization runs in more than one workgroup per block; batches that the
- * library factors with its panel path have no waits).  Returns
+ * factorization runs in more than one workgroup per block).  Returns
  * SOAP_ERR_HPARAM for other bits. */
 int soap_test_force_qr_give_up(uint32_t mask);
 

@@ -193,7 +193,7 @@ struct QrSplitOut {
 size_t qr_workspace_bytes(int64_t batch, int64_t n);
 void qr_force_give_up(unsigned mask);
 // Whether a call over `batch` matrices of order n runs the resident block
-// factorization on the current device (else the slower panel path).
+// factorization on the current device with one launch per block.
 hipError_t qr_block_path(int64_t batch, int64_t n, bool *out);
 hipError_t qr_factor_and_form_q(float *At, float *Q, float *Rf, int64_t batch, int64_t n,
                                 void *ws, size_t ws_bytes, hipStream_t s, hipStream_t sp,

@@ -11,8 +11,9 @@
 //  * An outer block is factored by qr_block_kernel: one launch whose
 //    workgroups keep the block in registers and sum the dot products of each
 //    column grid-wide (see the comment above the kernel).  It needs all of
-//    its workgroups resident; batches too large for that take the panel
-//    path:
+//    a launch's workgroups resident; larger batches take several launches.
+//    A device (partition) that cannot hold one matrix's workgroups takes the
+//    panel path:
 //  * Panel path: inner panels of width b in {16, 8, 4} are each factored by
 //    ONE 512-thread workgroup that holds the whole panel (rows ci..n-1, b
 //    columns) in registers (wave64 butterfly reductions, two barriers per
@@ -1763,9 +1764,10 @@ QrLayout qr_layout(int64_t batch, int64_t n) {
   L.fv_off = o;   o = align256(o + sizeof(float) * batch * L.sFv);
   // The resident-block path needs every workgroup of a launch resident at
   // once: at most BK_MAX_WG workgroups (two such launches, one per factor,
-  // may run together on the 256 compute units).
+  // may run together on the 256 compute units); a batch of more takes several
+  // launches per block.
   const int64_t P0 = (n + BK_ROWS - 1) / BK_ROWS;
-  L.block = P0 <= BK_MAX_P && P0 * batch <= BK_MAX_WG;
+  L.block = P0 <= BK_MAX_P && P0 <= BK_MAX_WG;
   L.x_off = o;
   if (L.block) o = align256(o + sizeof(unsigned) * batch * bk_xstride(n));
   L.total = o;
@@ -1833,6 +1835,7 @@ struct QrCtx {
   int ni;
   QrLayout L;
   int cap_small;             // workgroups a small-R block launch may use
+  int cap_big;               // ... and one launch of the other kernels
   const unsigned *skip;      // per-matrix failed flags (stride sSkip words), or nullptr
   int64_t sSkip;
   unsigned *status;
@@ -1858,33 +1861,49 @@ int narrow_split(int64_t M, int64_t N, int64_t K, int64_t batch, int64_t cap_flo
   return (int)std::max<int64_t>(1, s);
 }
 
-// Workgroups of block ob's resident-block launch and whether it takes the
-// small-R kernel.
+// Workgroups per matrix of block ob's resident-block launch and whether it
+// takes the small-R kernel (whose launches hold the whole batch).
 int block_launch_p(const QrCtx &x, int64_t ob, bool *small) {
   const int64_t c = ob * NB;
   const int Ps = (int)((x.n - c + BK_ROWS_SMALL - 1) / BK_ROWS_SMALL);
-  *small = Ps <= BK_SMALL_MAX_P && Ps * x.batch <= x.cap_small;
+  *small = Ps == 1 || (Ps <= BK_SMALL_MAX_P && Ps * x.batch <= x.cap_small);
   return *small ? Ps : (int)((x.n - c + BK_ROWS - 1) / BK_ROWS);
 }
 
 // Factors outer block ob on stream s (resident-block kernel or panel path).
+// A batch whose workgroups cannot all be resident takes several launches in
+// turn, each over as many matrices as can be (any number when a matrix is
+// one workgroup, which waits for nobody).  On 64 x (2048 x 768) the panel path
+// takes 62 ms of panel kernels per step (one workgroup per matrix and panel,
+// 176 panels), these launches 22 ms: the step 78.0 -> 51.8 ms (64 x 1024^2
+// 37.6 -> 19.5 with the faster products, 512 x 128^2 7.2 -> 1.7).  Up to 128
+// workgroups per launch gave 49.9 ms, but left no compute unit to others.
 hipError_t factor_block(const QrCtx &x, int64_t ob, hipStream_t s) {
   if (!x.L.block) return panel_phase(x, ob, s);
   const int c = (int)(ob * NB);
   const int nb = (int)std::min<int64_t>(NB, x.n - c);
   bool small = false;
   const int P = block_launch_p(x, ob, &small);
-  BlockParams bp{x.At, x.sA, x.ni, c, nb, x.Tb + ob * NB * NB, x.L.sT, x.Rf, x.dsign, x.betas,
-                 x.xch, bk_xstride(x.n), bk_area_words(x.n), (int)(ob & 1), P,
-                 x.status, x.status_bit};
-  const dim3 grid((unsigned)P, (unsigned)x.batch);
-  if (small)
-    hipLaunchKernelGGL((qr_block_kernel<BK_R_SMALL, BK_K_SMALL>), grid, dim3(BK_THREADS), 0, s, bp);
-  else if (P <= BK_MID_MAX_P)
-    hipLaunchKernelGGL((qr_block_kernel<BK_R, BK_K_MID>), grid, dim3(BK_THREADS), 0, s, bp);
-  else
-    hipLaunchKernelGGL((qr_block_kernel<BK_R, BK_K_BIG>), grid, dim3(BK_THREADS), 0, s, bp);
-  return hipGetLastError();
+  const int64_t xs = bk_xstride(x.n);
+  const int64_t per = P == 1 ? x.batch : std::max<int64_t>(1, x.cap_big / P);
+  const int64_t launches = (x.batch + per - 1) / per;
+  const int64_t step = (x.batch + launches - 1) / launches;   // of equal size
+  for (int64_t b0 = 0; b0 < x.batch; b0 += step) {
+    BlockParams bp{x.At + b0 * x.sA, x.sA, x.ni, c, nb, x.Tb + b0 * x.L.sT + ob * NB * NB, x.L.sT,
+                   x.Rf ? x.Rf + b0 * x.sA : nullptr, x.dsign + b0 * x.n, x.betas + b0 * x.n,
+                   x.xch + b0 * xs, xs, bk_area_words(x.n), (int)(ob & 1), P, x.status,
+                   x.status_bit};
+    const dim3 grid((unsigned)P, (unsigned)std::min(step, x.batch - b0));
+    if (small)
+      hipLaunchKernelGGL((qr_block_kernel<BK_R_SMALL, BK_K_SMALL>), grid, dim3(BK_THREADS), 0, s,
+                         bp);
+    else if (P <= BK_MID_MAX_P)
+      hipLaunchKernelGGL((qr_block_kernel<BK_R, BK_K_MID>), grid, dim3(BK_THREADS), 0, s, bp);
+    else
+      hipLaunchKernelGGL((qr_block_kernel<BK_R, BK_K_BIG>), grid, dim3(BK_THREADS), 0, s, bp);
+    SOAP_TRY(hipGetLastError());
+  }
+  return hipSuccess;
 }
 
 // Factors the columns of outer block ob (inner panels, their row-parallel
@@ -2260,13 +2279,17 @@ hipError_t qr_factor_and_form_q(float *At, float *Q, float *Rf, int64_t batch, i
   if (ws_bytes < x.L.total) return hipErrorInvalidValue;
   if (split && (Rf || batch != 2 * split->half || !split->QA || !split->QB))
     return hipErrorInvalidValue;
-  x.cap_small = BK_MAX_WG;
-  if (x.L.block) {   // resident blocks only where the device holds them all at once
-    SOAP_TRY(qr_block_path(batch, n, &x.L.block));
+  x.cap_small = x.cap_big = BK_MAX_WG;
+  if (x.L.block) {   // resident blocks only where the device holds a matrix's all at once
     hipError_t err = hipSuccess;
+    const int cap_big = resident_cap(false, &err);
+    if (err != hipSuccess) return err;
     const int cap_small = resident_cap(true, &err);
     if (err != hipSuccess) return err;
+    const int64_t P0 = (n + BK_ROWS - 1) / BK_ROWS;
+    x.L.block = P0 <= std::min(BK_MAX_WG, cap_big);
     x.cap_small = std::min(BK_MAX_WG, cap_small);
+    x.cap_big = std::min(BK_MAX_WG, cap_big);
   }
   // (with two destinations the scatter of the Q's reports failures per half)
   x.status = split ? nullptr : status;

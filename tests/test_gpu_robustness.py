@@ -294,10 +294,9 @@ def test_checkpoint_resume_is_bitwise(kl, batch):
         assert np.array_equal(a[key], b[key]), key
 
 
-def test_panel_path_ignores_what_other_kernels_left_in_lds():
-    """64 matrices take the QR's panel path; the step after products of NaN
-    matrices (whose LDS holds NaN on every compute unit) is bit for bit the
-    step before them."""
+def test_batched_step_ignores_what_other_kernels_left_in_lds():
+    """The step of 64 matrices after products of NaN matrices (whose LDS holds
+    NaN on every compute unit) is bit for bit the step before them."""
     import torch
     import paper_2607_20548_amd as soap
     batch, m, n = 64, 300, 260
@@ -318,3 +317,26 @@ def test_panel_path_ignores_what_other_kernels_left_in_lds():
     for a, b in zip(*out):
         assert torch.isfinite(a).all()
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("batch,m,n", [(97, 130, 100), (50, 513, 300), (33, 300, 770)])
+def test_batches_of_several_block_launches(batch, m, n):
+    """Batches whose workgroups exceed one resident launch (several launches
+    per block, the last one smaller; one-workgroup matrices in one): entries
+    of every launch equal the same matrix stepped alone."""
+    import paper_2607_20548_amd as soap
+    G = np.stack([next(iter(_grads(m, n, 1, b))) for b in range(3)])[np.arange(batch) % 3]
+    W0 = 0.02 * np.random.default_rng(2).standard_normal((batch, m, n))
+    st = soap.SoapState(m, n, batch=batch)
+    W, Gd = dev(W0), dev(G)
+    for t in (1, 2):
+        st.step(W, Gd, t, **HP)
+    assert st.status()[0] == soap.SOAP_OK
+    for b in (0, batch // 2, batch - 1):
+        one = soap.SoapState(m, n)
+        w1 = dev(W0[b])
+        for t in (1, 2):
+            one.step(w1, dev(G[b]), t, **HP)
+        for name in ("Q_L", "Q_R", "V"):
+            assert rel(host(getattr(st, name)[b]), host(getattr(one, name))) <= 1e-5, (b, name)
+        assert rel(host(W[b]), host(w1)) <= 1e-5, b
