@@ -189,3 +189,22 @@ def test_bf16_muon_fullsize_against_fp32_path():
     log(f"bf16 vs fp32 Newton-Schulz at 4096x14336: {e:.3e}")
     assert e <= 0.1
     assert torch.isfinite(out[True]).all().item()
+
+
+@pytest.mark.parametrize("batch,m,n", [(48, 264, 520), (48, 520, 264), (130, 256, 256),
+                                       (44, 272, 1000), (130, 128, 72)])
+def test_tile_sizes_agree_bit_for_bit(batch, m, n):
+    """A batch large enough for 256-tiles (K a multiple of 64 and not, ragged
+    last tiles, mirrored triangles) against its entries alone, which take the
+    small tiles: every tile size sums over k in the same order."""
+    import torch
+    import paper_2607_20548_amd as soap
+    g = torch.Generator(device="cuda").manual_seed(m + n)
+    G = torch.randn(batch, m, n, generator=g, device="cuda")
+    coeffs = [(15 / 8, -5 / 4, 3 / 8)] * 3 + [(1.5, -0.5, 0.0)]
+    W = torch.zeros(batch, m, n, device="cuda")
+    soap.MuonState(m, n, batch=batch).step(W, G, coeffs, bf16=True)
+    for b in (0, batch // 2, batch - 1):
+        w1 = torch.zeros(m, n, device="cuda")
+        soap.MuonState(m, n).step(w1, G[b].contiguous(), coeffs, bf16=True)
+        assert torch.isfinite(w1).all() and torch.equal(W[b], w1), b
