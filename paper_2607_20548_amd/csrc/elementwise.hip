@@ -61,14 +61,6 @@ __global__ __launch_bounds__(EW_THREADS) void zero_u32_kernel(uint32_t *p, int64
     p[i] = 0u;
 }
 
-__global__ __launch_bounds__(EW_THREADS) void copy_kernel(float *__restrict__ d,
-                                                          const float *__restrict__ s,
-                                                          int64_t n) {
-  for (int64_t i = blockIdx.x * (int64_t)EW_THREADS + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * EW_THREADS)
-    d[i] = s[i];
-}
-
 }  // namespace
 
 hipError_t launch_momentum(float *M, const float *G, int64_t count, float b1, hipStream_t s) {
@@ -97,13 +89,6 @@ hipError_t launch_fill_diag(float *X, int64_t batch, int64_t r, int64_t c, int64
 hipError_t launch_zero_u32(uint32_t *p, int64_t count, hipStream_t s) {
   if (count <= 0) return hipSuccess;
   hipLaunchKernelGGL(zero_u32_kernel, dim3(ew_blocks(count)), dim3(EW_THREADS), 0, s, p, count);
-  return hipGetLastError();
-}
-
-hipError_t launch_copy(float *dst, const float *src, int64_t count, hipStream_t s) {
-  if (count <= 0) return hipSuccess;
-  hipLaunchKernelGGL(copy_kernel, dim3(ew_blocks(count)), dim3(EW_THREADS), 0, s, dst, src,
-                     count);
   return hipGetLastError();
 }
 

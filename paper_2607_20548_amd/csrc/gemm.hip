@@ -84,6 +84,8 @@ struct KParams {
   float *C;
   int64_t ldc, sC;
   float alpha, beta;
+  const float *D;   // what beta applies to (C unless the caller gave another)
+  int64_t ldd, sD;
   float *V;
   float *Nout;
   float b2, c1, c2, eps;
@@ -403,6 +405,7 @@ __global__ __launch_bounds__(NTHREADS, BT == BIG ? 2 : 3) void gemm_f32_split(KP
   // Epilogue.  Accumulator register r of block (i, j) holds
   // C[row0 + 8*(r/4) + 4*h + r%4][col0 + xl].
   float *C = p.C + bz * p.sC;
+  const float *Dm = p.D + bz * p.sD;
   float *P = p.part ? p.part + (bz * gridDim.y + blockIdx.y) * (int64_t)p.M * p.N : nullptr;
   float *V = (MODE == MODE_ADAM) ? p.V + bz * p.sC : nullptr;
   float *Nout = (MODE == MODE_ADAM) ? p.Nout + bz * p.sC : nullptr;
@@ -410,7 +413,8 @@ __global__ __launch_bounds__(NTHREADS, BT == BIG ? 2 : 3) void gemm_f32_split(KP
   constexpr int NQ = WT * BT / 4 / NTHREADS;   // float4 of a half per thread
   constexpr int QG = NQ < 4 ? NQ : 4;
   if constexpr (MODE == MODE_SYRK) {
-   if ((reinterpret_cast<uintptr_t>(C) & 15u) == 0 && (p.ldc & 3) == 0) {
+   if (!P && ((reinterpret_cast<uintptr_t>(C) | reinterpret_cast<uintptr_t>(Dm)) & 15u) == 0 &&
+       ((p.ldc | p.ldd) & 3) == 0) {
     staged = true;
     // One triangle, mirrored, through LDS in two halves of WT rows: the
     // lower part (row >= col) is written as beta C + alpha acc with 16-byte
@@ -445,7 +449,7 @@ __global__ __launch_bounds__(NTHREADS, BT == BIG ? 2 : 3) void gemm_f32_split(KP
           // only the lower triangle is read (a float4 with col <= row holds at
           // least one element of it; the others are masked)
           if (read_back && row < p.M && col <= row && col < p.N) {
-            const float *src = C + (int64_t)row * p.ldc + col;
+            const float *src = Dm + (int64_t)row * p.ldd + col;
             if (col + 3 < p.N && col + 3 <= row) {
               cv[qq] = *reinterpret_cast<const float4 *>(src);
             } else {
@@ -512,7 +516,8 @@ __global__ __launch_bounds__(NTHREADS, BT == BIG ? 2 : 3) void gemm_f32_split(KP
    }
   }
   if constexpr (MODE == MODE_GENERAL) {
-   if (!P && (reinterpret_cast<uintptr_t>(C) & 15u) == 0 && (p.ldc & 3) == 0) {
+   if (!P && ((reinterpret_cast<uintptr_t>(C) | reinterpret_cast<uintptr_t>(Dm)) & 15u) == 0 &&
+       ((p.ldc | p.ldd) & 3) == 0) {
     staged = true;
     // Rank-k updates are bound by their pass over C, so the tile goes
     // through LDS (free after the K loop) in two halves of WT rows and C is
@@ -541,7 +546,7 @@ __global__ __launch_bounds__(NTHREADS, BT == BIG ? 2 : 3) void gemm_f32_split(KP
         const int row = m0 + half * WT + lrow, col = n0 + c4;
         cv[q] = make_float4(0.f, 0.f, 0.f, 0.f);
         if (read_back && row < p.M) {
-          const float *src = C + (int64_t)row * p.ldc + col;
+          const float *src = Dm + (int64_t)row * p.ldd + col;
           if (col + 3 < p.N) {
             cv[q] = *reinterpret_cast<const float4 *>(src);
           } else {
@@ -594,7 +599,7 @@ __global__ __launch_bounds__(NTHREADS, BT == BIG ? 2 : 3) void gemm_f32_split(KP
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
             const int row = m0 + wm * WT + i * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
-            cv[r] = (p.beta != 0.f && row < p.M && col < p.N) ? C[(int64_t)row * p.ldc + col] : 0.f;
+            cv[r] = (p.beta != 0.f && row < p.M && col < p.N) ? Dm[(int64_t)row * p.ldd + col] : 0.f;
           }
         }
         asm volatile("" ::: "memory");
@@ -603,7 +608,7 @@ __global__ __launch_bounds__(NTHREADS, BT == BIG ? 2 : 3) void gemm_f32_split(KP
           const int row = m0 + wm * WT + i * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
           if (row >= p.M || col >= p.N) continue;
           const int64_t off = (int64_t)row * p.ldc + col;
-          if (MODE == MODE_GENERAL && P) {
+          if (MODE != MODE_ADAM && P) {
             P[(int64_t)row * p.N + col] = acc[i][j][r];
           } else if (MODE == MODE_GENERAL) {
             float v = p.alpha * acc[i][j][r];
@@ -611,7 +616,7 @@ __global__ __launch_bounds__(NTHREADS, BT == BIG ? 2 : 3) void gemm_f32_split(KP
             C[off] = v;
           } else if (MODE == MODE_SYRK) {
             if (row < col) continue;  // the mirror of (col,row) is written by its owner
-            const float v = (p.beta != 0.f ? p.beta * C[off] : 0.f) + p.alpha * acc[i][j][r];
+            const float v = (p.beta != 0.f ? p.beta * Dm[(int64_t)row * p.ldd + col] : 0.f) + p.alpha * acc[i][j][r];
             C[off] = v;
             if (row != col) C[(int64_t)col * p.ldc + row] = v;
           } else if ((r & 1) == 0) {
@@ -650,6 +655,41 @@ __global__ __launch_bounds__(256) void splitk_reduce(const float *__restrict__ p
     float v = alpha * acc;
     if (beta != 0.f) v += beta * Cb[row * ldc + col];
     Cb[row * ldc + col] = v;
+  }
+}
+
+// The same for the lower triangle of a symmetric product: the sum of every
+// element with row >= col goes to (row, col) and (col, row), by 32 x 32 blocks
+// on or below the diagonal (the mirror through LDS).
+__global__ __launch_bounds__(256) void splitk_reduce_syrk(const float *__restrict__ part, int S,
+                                                          int N, float *C, int64_t ldc, int64_t sC,
+                                                          const float *D, int64_t ldd, int64_t sD,
+                                                          float alpha, float beta) {
+  __shared__ float tile[32][33];
+  const int bi = blockIdx.y, bj = blockIdx.x;
+  if (bj > bi) return;
+  const int64_t bz = blockIdx.z, nn = (int64_t)N * N;
+  const float *pb = part + bz * S * nn;
+  float *Cb = C + bz * sC;
+  const float *Db = D + bz * sD;
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int row = 32 * bi + ty + 8 * q, col = 32 * bj + tx;
+    float v = 0.f;
+    if (row < N && col <= row) {
+      for (int s = 0; s < S; ++s) v += pb[s * nn + (int64_t)row * N + col];
+      v *= alpha;
+      if (beta != 0.f) v += beta * Db[(int64_t)row * ldd + col];
+      Cb[(int64_t)row * ldc + col] = v;
+    }
+    tile[ty + 8 * q][tx] = v;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int col = 32 * bj + ty + 8 * q, row = 32 * bi + tx;
+    if (row < N && row > col) Cb[(int64_t)col * ldc + row] = tile[tx][ty + 8 * q];
   }
 }
 
@@ -708,7 +748,7 @@ void set_tiles(KParams &kp, int bt, bool triangle) {
 template <int MODE>
 hipError_t dispatch(const GemmDesc &d, KParams &kp, hipStream_t s, bool aligned) {
   hipError_t err;
-  const int S = (MODE == MODE_GENERAL && d.splitk > 1 && d.part) ? d.splitk : 1;
+  const int S = (MODE != MODE_ADAM && d.splitk > 1 && d.part) ? d.splitk : 1;
   // A cap counts every workgroup (split slices and batch included); the
   // tile dimension stays a multiple of 8 for XCD locality.
   const int64_t per_tile = (int64_t)S * d.batch;
@@ -734,6 +774,12 @@ hipError_t dispatch(const GemmDesc &d, KParams &kp, hipStream_t s, bool aligned)
     }
   }
   if (err != hipSuccess || S == 1 || d.partials_only) return err;
+  if (MODE == MODE_SYRK) {
+    const unsigned g = (unsigned)((d.N + 31) / 32);
+    hipLaunchKernelGGL(splitk_reduce_syrk, dim3(g, g, (unsigned)d.batch), dim3(256), 0, s, kp.part,
+                       S, kp.N, kp.C, kp.ldc, kp.sC, kp.D, kp.ldd, kp.sD, d.alpha, d.beta);
+    return hipGetLastError();
+  }
   int64_t mn = d.M * d.N;
   unsigned gx = (unsigned)std::min<int64_t>((mn + 255) / 256, 2048);
   hipLaunchKernelGGL(splitk_reduce, dim3(gx, (unsigned)d.batch), dim3(256), 0, s, kp.part, S,
@@ -748,6 +794,9 @@ KParams make_params(const GemmDesc &d, bool triangle = false) {
   kp.B = d.B; kp.ldb = d.ldb; kp.sB = d.sB;
   kp.C = d.C; kp.ldc = d.ldc; kp.sC = d.sC;
   kp.alpha = d.alpha; kp.beta = d.beta;
+  kp.D = d.D ? d.D : d.C;
+  kp.ldd = d.D ? d.ldd : d.ldc;
+  kp.sD = d.D ? d.sD : d.sC;
   set_tiles(kp, BIG, triangle);
   kp.kslice = (int)d.K;
   kp.part = nullptr;
@@ -793,8 +842,15 @@ int choose_splitk(int64_t M, int64_t N, int64_t K, int64_t batch, int max_split)
   return (int)s;
 }
 
+// (517^2 triangle, K = 1283, 45 64-tiles: the Newton-Schulz Gram product.)
+int choose_syrk_split(int64_t d, int64_t K, int64_t batch) {
+  const int64_t t = (d + SMALL - 1) / SMALL, tiles = t * (t + 1) / 2 * batch;
+  return (int)std::max<int64_t>(1, std::min<int64_t>({8, 512 / std::max<int64_t>(1, tiles), K / 256}));
+}
+
 hipError_t launch_gemm(const GemmDesc &d, hipStream_t s) {
   if (d.M <= 0 || d.N <= 0 || d.batch <= 0) return hipSuccess;
+  if (d.D && d.splitk > 1) return hipErrorInvalidValue;
   KParams kp = make_params(d);
   return dispatch<MODE_GENERAL>(d, kp, s, aligned_loads(d));
 }

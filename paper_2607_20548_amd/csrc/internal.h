@@ -26,6 +26,10 @@ struct GemmDesc {
   float *C = nullptr;
   int64_t ldc = 0, sC = 0;
   float alpha = 1.f, beta = 0.f;
+  // If set, beta applies to D instead of C: C = alpha op(A) op(B) + beta D (not
+  // with split-K of a general product, nor in the Adam form).
+  const float *D = nullptr;
+  int64_t ldd = 0, sD = 0;
   int64_t batch = 1;
   // Split-K: when splitk > 1 the K range is cut into `splitk` slices whose
   // partial products go to `part` (batch * splitk * M * N floats) and are then
@@ -52,6 +56,10 @@ struct GemmDesc {
 // the given tile count and K, capped by the partial buffer `max_split`.
 int choose_splitk(int64_t M, int64_t N, int64_t K, int64_t batch, int max_split);
 
+// A split-K factor for launch_syrk_ema on a d x d triangle with few tiles and
+// long K (1: not split): about two 64-tiles per CU, at least 256 of K each.
+int choose_syrk_split(int64_t d, int64_t K, int64_t batch);
+
 // C = alpha op(A) op(B) + beta C (C not read when beta == 0).
 hipError_t launch_gemm(const GemmDesc &d, hipStream_t s);
 
@@ -59,7 +67,8 @@ hipError_t launch_gemm(const GemmDesc &d, hipStream_t s);
 // op(A) op(B) is symmetric (op(B) = op(A)^T, or op(A) D op(A)^T with the
 // diagonal scaling folded into B), only tiles on or below the diagonal are
 // computed and each result is stored at (i,j) and (j,i).  C is read from its
-// lower triangle.  max_wg caps it like a GEMM for the layouts (0, 1) and (1, 0).
+// lower triangle (or D, if set, from its).  max_wg caps it like a GEMM for the
+// layouts (0, 1) and (1, 0).  With split-K the partials hold the lower tiles.
 hipError_t launch_syrk_ema(const GemmDesc &d, hipStream_t s);
 
 // Fused second rotation + Adam in the eigenbasis.  op(A) (trans_a = 0,
@@ -85,8 +94,6 @@ hipError_t launch_fill_diag(float *X, int64_t batch, int64_t r, int64_t c, int64
                             float diag_value, hipStream_t s);
 // Zero `count` 32-bit words.
 hipError_t launch_zero_u32(uint32_t *p, int64_t count, hipStream_t s);
-// Copy `count` floats.
-hipError_t launch_copy(float *dst, const float *src, int64_t count, hipStream_t s);
 
 // ------------------------------------------------------------ KL factors
 // lambda[b][k] = sum_i X[b][k][i] Q[b][i][k] for `batch` d x d row-major X, Q

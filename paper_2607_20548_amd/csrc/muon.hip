@@ -13,7 +13,7 @@ constexpr int NR_BLOCKS = 1024;  // partial sums per matrix (fixed: the order is
 // Sum of squares of each matrix's `count` floats: block j of matrix b covers
 // a fixed contiguous range (a multiple of 4 floats, read as float4 when the
 // matrix is 16-byte aligned), accumulates in double, and reduces in a fixed
-// tree; norm_finish adds the NR_BLOCKS partials in index order.
+// tree; norm_finish adds the NR_BLOCKS partials in a fixed order.
 __global__ __launch_bounds__(NR_THREADS) void norm_partial(const float *__restrict__ X,
                                                           int64_t count, double *__restrict__ part) {
   __shared__ double red[NR_THREADS];
@@ -43,13 +43,23 @@ __global__ __launch_bounds__(NR_THREADS) void norm_partial(const float *__restri
   if (threadIdx.x == 0) part[b * NR_BLOCKS + blockIdx.x] = red[0];
 }
 
-// inv[b] = 1 / max(sqrt(sum of squares), eps)
+// inv[b] = 1 / max(sqrt(sum of squares), eps): one wave per matrix, lane l adds
+// NR_BLOCKS / 64 consecutive partials in order, the lanes in a fixed tree (one
+// thread adding all 1024 took 16 us of loads in turn).
 __global__ __launch_bounds__(64) void norm_finish(const double *__restrict__ part, int64_t batch,
                                                   float eps, float *__restrict__ inv) {
-  const int64_t b = (int64_t)blockIdx.x * 64 + threadIdx.x;
-  if (b >= batch) return;
+  constexpr int PER = NR_BLOCKS / 64;
+  const int64_t b = blockIdx.x;
+  const double *pb = part + b * NR_BLOCKS + threadIdx.x * PER;
+  double v[PER];
+#pragma unroll
+  for (int j = 0; j < PER; ++j) v[j] = pb[j];
   double s = 0.0;
-  for (int j = 0; j < NR_BLOCKS; ++j) s += part[b * NR_BLOCKS + j];
+#pragma unroll
+  for (int j = 0; j < PER; ++j) s += v[j];
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) s += __shfl_xor(s, m);
+  if (threadIdx.x != 0) return;
   const double nrm = sqrt(s);
   inv[b] = (float)(1.0 / (nrm > (double)eps ? nrm : (double)eps));
 }
@@ -92,7 +102,7 @@ hipError_t launch_muon_normalise(const float *M, float *X, int64_t batch, int64_
                      count, part);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(norm_finish, dim3((unsigned)((batch + 63) / 64)), dim3(64), 0, s, part,
+  hipLaunchKernelGGL(norm_finish, dim3((unsigned)batch), dim3(64), 0, s, part,
                      batch, eps, inv);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   hipLaunchKernelGGL(scale_by_inv, dim3(grid_for(count, batch), (unsigned)batch), dim3(256), 0, s,
@@ -107,7 +117,7 @@ hipError_t launch_muon_norm_inv(const float *M, int64_t batch, int64_t count, fl
                      count, part);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(norm_finish, dim3((unsigned)((batch + 63) / 64)), dim3(64), 0, s, part,
+  hipLaunchKernelGGL(norm_finish, dim3((unsigned)batch), dim3(64), 0, s, part,
                      batch, eps, inv);
   return hipGetLastError();
 }

@@ -804,7 +804,8 @@ int step_impl(int64_t batch, float *param, const float *grad, float *L, float *R
 
 // ------------------------------------------------------------------ Muon
 struct MuonLayout {
-  size_t x, xn, a, bm, part, inv, total;
+  size_t x, xn, a, bm, part, inv, sk, total;
+  int split;   // K slices of the fp32 Gram product (sk: their partials)
 };
 
 MuonLayout muon_layout(int64_t batch, int64_t m, int64_t n) {
@@ -818,6 +819,8 @@ MuonLayout muon_layout(int64_t batch, int64_t m, int64_t n) {
   L.bm = o; o = align256(o + f * batch * d * d);
   L.part = o; o = align256(o + soap::muon_norm_partial_bytes(batch));
   L.inv = o; o = align256(o + f * batch);
+  L.split = soap::choose_syrk_split(d, std::max(m, n), batch);
+  L.sk = o; o = align256(o + (L.split > 1 ? f * batch * L.split * d * d : 0));
   L.total = o;
   return L;
 }
@@ -971,22 +974,24 @@ int muon_impl(int64_t batch, float *param, const float *grad, float *M, int64_t 
       g.M = d; g.N = d; g.K = e2;
       g.A = X; g.lda = n; g.sA = mn; g.B = X; g.ldb = n; g.sB = mn;
       g.C = A; g.ldc = d; g.sC = dd; g.alpha = 1.f; g.beta = 0.f; g.batch = batch;
+      g.splitk = lay.split;
+      g.part = reinterpret_cast<float *>(w + lay.sk);
       if ((e = soap::launch_syrk_ema(g, s)) != hipSuccess) return hip_fail(e, "Newton-Schulz A");
     }
     const float *Bop = A;
     float alpha_b = b;
-    if (c != 0.f) {  // B = b A + c A^2
-      if ((e = soap::launch_copy(Bm, A, batch * dd, s)) != hipSuccess) return hip_fail(e, "copy");
+    if (c != 0.f) {  // B = b A + c A^2 (A symmetric: one triangle of A A^T)
       soap::GemmDesc g;
+      g.trans_a = 0; g.trans_b = 1;
       g.M = d; g.N = d; g.K = d;
       g.A = A; g.lda = d; g.sA = dd; g.B = A; g.ldb = d; g.sB = dd;
       g.C = Bm; g.ldc = d; g.sC = dd; g.alpha = c; g.beta = b; g.batch = batch;
-      if ((e = soap::launch_gemm(g, s)) != hipSuccess) return hip_fail(e, "Newton-Schulz B");
+      g.D = A; g.ldd = d; g.sD = dd;
+      if ((e = soap::launch_syrk_ema(g, s)) != hipSuccess) return hip_fail(e, "Newton-Schulz B");
       Bop = Bm;
       alpha_b = 1.f;
     }
     // X <- a X + B X (wide) or a X + X B (tall)
-    if ((e = soap::launch_copy(Xn, X, batch * mn, s)) != hipSuccess) return hip_fail(e, "copy");
     soap::GemmDesc g;
     g.M = m; g.N = n; g.K = d;
     if (tall) {
@@ -995,6 +1000,7 @@ int muon_impl(int64_t batch, float *param, const float *grad, float *M, int64_t 
       g.A = Bop; g.lda = d; g.sA = dd; g.B = X; g.ldb = n; g.sB = mn;
     }
     g.C = Xn; g.ldc = n; g.sC = mn; g.alpha = alpha_b; g.beta = a; g.batch = batch;
+    g.D = X; g.ldd = n; g.sD = mn;
     if ((e = soap::launch_gemm(g, s)) != hipSuccess) return hip_fail(e, "Newton-Schulz X");
     std::swap(X, Xn);
   }

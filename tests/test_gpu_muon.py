@@ -122,3 +122,26 @@ def test_muon_bench_shape():
     spec = sg.workload(2).matrices[0]
     G = next(sg.make_matrix_stream(spec, 2, 1))
     _run(spec.m, spec.n, [G], sg.initial_weight(spec, 2), QUINTIC, tag="bench")
+
+
+@pytest.mark.parametrize("batch,m,n", [(1, 130, 1030), (1, 2051, 65), (3, 100, 515), (1, 520, 520),
+                                       (2, 1100, 1000)])
+def test_gram_products_split_over_k(batch, m, n):
+    """Wide and tall weights whose Gram product is split over K (edges of the
+    64-tiles and of the slices), square ones whose is not: one step against the
+    fp64 iteration."""
+    import torch
+    import paper_2607_20548_amd as soap
+    g = torch.Generator(device="cuda").manual_seed(m)
+    G = torch.randn(batch, m, n, generator=g, device="cuda")
+    coeffs = [(15 / 8, -5 / 4, 3 / 8)] * 4
+    shape = (batch, m, n) if batch > 1 else (m, n)
+    W = torch.zeros(shape, device="cuda")
+    soap.MuonState(m, n, batch=batch).step(W, G.view(shape), coeffs, lr=1.0, weight_decay=0.0)
+    X = 0.1 * G.double()
+    X = X / X.flatten(1).norm(dim=1).view(-1, 1, 1)
+    for a, b, c in coeffs:
+        S = X @ X.mT
+        X = a * X + (b * S + c * S @ S) @ X
+    want = -(max(m, n) ** 0.5) * X.view(shape)
+    assert float((W.double() - want).norm() / want.norm()) <= 2e-6
