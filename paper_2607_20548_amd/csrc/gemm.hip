@@ -842,10 +842,20 @@ int choose_splitk(int64_t M, int64_t N, int64_t K, int64_t batch, int max_split)
   return (int)s;
 }
 
-// (517^2 triangle, K = 1283, 45 64-tiles: the Newton-Schulz Gram product.)
+// A triangle of at most 256 64-tiles is split into about two workgroups per CU
+// of at least 256 of K each (517^2, K = 1283, 45 tiles: 80 -> 27 + 8 us); one of
+// more, but of few 128-tiles (whose compute units would hold one tile or
+// none), into 128-tiles of at least 1024 of K each where two slices or more
+// fit two workgroups per CU (2048^2, K = 8192, 136 of them: the Muon step of
+// 2048 x 8192 13.0 -> 11.6 ms).
 int choose_syrk_split(int64_t d, int64_t K, int64_t batch) {
-  const int64_t t = (d + SMALL - 1) / SMALL, tiles = t * (t + 1) / 2 * batch;
-  return (int)std::max<int64_t>(1, std::min<int64_t>({8, 512 / std::max<int64_t>(1, tiles), K / 256}));
+  const int64_t t1 = (d + SMALL - 1) / SMALL, n1 = t1 * (t1 + 1) / 2 * batch;
+  const int64_t t2 = (d + BIG - 1) / BIG, n2 = t2 * (t2 + 1) / 2 * batch;
+  if (n1 <= 0) return 1;
+  int64_t s = 1;
+  if (n1 <= 256) s = std::min<int64_t>({8, 512 / n1, K / 256});
+  else if (n2 * 2 > SMALL_MAX_TILES) s = std::min<int64_t>({8, 512 / n2, K / 1024});
+  return (int)std::max<int64_t>(1, s);
 }
 
 hipError_t launch_gemm(const GemmDesc &d, hipStream_t s) {
