@@ -23,6 +23,7 @@
 #include "internal.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace soap {
 namespace {
@@ -215,30 +216,37 @@ __global__ __launch_bounds__(NTH, 2) void gemm_bf16_nt(BfParams p) {
     }
 }
 
-// The same product by 256 x 256 tiles: 512 threads, 8 waves (2 x 4), each
-// 128 x 64 as 4 x 2 accumulators.  A wave reads 6 KB of LDS for 8 matrix
-// instructions instead of 8 KB, and a slab is read from memory half as
-// often per flop.  K advances in slabs of 64 through two LDS buffers of
-// unpadded 128-byte rows whose 16-byte units are permuted (unit g of row x at
-// g ^ (x % 8)), so that eight consecutive rows of one g cover all banks; the
-// next slab is in flight (32 registers) while one is multiplied.  The
-// sums run over k in the same order as with 128-tiles: the results are the
-// same bit for bit.  Measured: B X of 4096 x 14336 750 -> 610 us (788
-// TFLOP/s), of 64 x (768 x 2048) 665 -> 360 us (with both layouts of the
-// result written, 170 us at the copy rate); one tile per CU, so its epilogue
-// runs alone.
+// The same product by 256 x 256 tiles: 256 threads, 4 waves (2 x 2), one per
+// SIMD, each 128 x 128 as 4 x 4 accumulators (256 of the 512 registers a lane
+// may hold).  A wave reads 8 KB of LDS for 16 matrix instructions: the reads
+// and the slab's writes take three quarters of the matrix instructions'
+// time, where eight waves of 128 x 64 took all of it (12 KB).  K advances in
+// slabs of 64 through two LDS buffers of unpadded 128-byte rows whose 16-byte
+// units are permuted (unit g of row x at g ^ (x % 8)), so that eight
+// consecutive rows of one g cover all banks.  With one wave per SIMD nothing
+// else hides a latency, so each of a slab's four steps of 16 k multiplies
+// fragments read during the step before, the first two steps also move the
+// next slab from registers to LDS and load the one after it (in flight for a
+// whole slab), and the barrier lies before the fourth step, which reads the
+// next slab's first fragments.  The sums run over k in the same order as
+// with 128-tiles: the results are the same bit for bit.  Measured against
+// 128-tiles and eight waves of 128 x 64: B X of 4096 x 14336 750, 610 -> 518 us
+// (928 TFLOP/s; 3.5 tiles per CU, so 1060 while the chip is full); of 64 x (768
+// x 2048), K = 768, 665, 360 -> 324 us, most of it the epilogue's pass over
+// memory, which one tile per CU leaves uncovered.
 // Epilogue: 64 rows at a time through LDS in fp32 (each result is rounded
-// once), D read and C written 16 bytes per lane, and the transposed output (C
-// itself mirrored in SYRK mode) from the columns of the same 64 rows.
+// once), D read (a band ahead) and C written 16 bytes per lane, and the
+// transposed output (C itself mirrored in SYRK mode) from the columns of the
+// same 64 rows.
 constexpr int T2 = 256;
-constexpr int NTH2 = 512;
 constexpr int OP2 = T2 * KB;                    // one operand slab, bfloat16 values
 constexpr int SLD2 = T2 + 4;                    // staging row in floats
 
 __device__ __forceinline__ int unit2(int x, int g) { return x * KB + 8 * (g ^ (x & 7)); }
 
-template <int MODE>
-__global__ __launch_bounds__(NTH2, 2) void gemm_bf16_nt256(BfParams p) {
+// TAIL: K is not a multiple of the slab.
+template <int MODE, bool TAIL>
+__global__ __launch_bounds__(NTH, 1) void gemm_bf16_nt256(BfParams p) {
   __shared__ __attribute__((aligned(16))) uint16_t lds[2 * 2 * OP2];
   static_assert(64 * SLD2 * 4 <= 2 * 2 * OP2 * 2, "the staging rows fit the slabs");
   int tm, tn;
@@ -248,73 +256,102 @@ __global__ __launch_bounds__(NTH2, 2) void gemm_bf16_nt256(BfParams p) {
   const uint16_t *Q = p.Q + bz * p.sQ;
   const int m0 = tm * T2, n0 = tn * T2;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 2, wn = wave & 3;
+  const int wm = wave >> 1, wn = wave & 1;
   const int xl = lane & 31, h = lane >> 5;
 
-  v16f acc[4][2];
+  v16f acc[4][4];
 #pragma unroll
   for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < 4; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-  // thread -> rows (tid >> 3) + 64 s, unit tid & 7 of each operand
+  // thread -> rows (tid >> 3) + 32 s, unit tid & 7 of each operand; slabs past
+  // the last are loaded from clamped addresses and never multiplied
   const int lr = tid >> 3, lg = tid & 7;
-  uint4 ra[4], rb[4];
-  const uint16_t *pa[4], *pb[4];
+  uint4 ra[8], rb[8];
+  const uint16_t *pa[8], *pb[8];
 #pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    pa[s] = P + (int64_t)min(m0 + lr + 64 * s, p.M - 1) * p.ldp;
-    pb[s] = Q + (int64_t)min(n0 + lr + 64 * s, p.N - 1) * p.ldq;
+  for (int s = 0; s < 8; ++s) {
+    pa[s] = P + (int64_t)min(m0 + lr + 32 * s, p.M - 1) * p.ldp;
+    pb[s] = Q + (int64_t)min(n0 + lr + 32 * s, p.N - 1) * p.ldq;
   }
-  auto load = [&](int k0) {
-    const int k = min(k0 + 8 * lg, p.K - 8);
+  auto load = [&](uint4 (&r)[8], const uint16_t *const (&src)[8], int kt) {
+    const int k = min(kt * KB + 8 * lg, p.K - 8);
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      ra[s] = *reinterpret_cast<const uint4 *>(pa[s] + k);
-      rb[s] = *reinterpret_cast<const uint4 *>(pb[s] + k);
+    for (int s = 0; s < 8; ++s) r[s] = *reinterpret_cast<const uint4 *>(src[s] + k);
+  };
+  auto store = [&](const uint4 (&r)[8], uint16_t *dst, int kt) {
+    const bool dead = TAIL && kt * KB + 8 * lg >= p.K;   // K % 8 == 0
+#pragma unroll
+    for (int s = 0; s < 8; ++s)
+      *reinterpret_cast<uint4 *>(dst + unit2(lr + 32 * s, lg)) =
+          dead ? make_uint4(0u, 0u, 0u, 0u) : r[s];
+  };
+  auto op = [&](int kt, int which) { return lds + ((kt & 1) * 2 + which) * OP2; };
+  v8bf fa[2][4], fb[2][4];
+  auto frag = [&](int f, int kt, int q) {
+    const uint16_t *la = op(kt, 0), *lb = op(kt, 1);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      fa[f][i] = __builtin_bit_cast(
+          v8bf, *reinterpret_cast<const uint4 *>(la + unit2(wm * 128 + 32 * i + xl, 2 * q + h)));
+      fb[f][i] = __builtin_bit_cast(
+          v8bf, *reinterpret_cast<const uint4 *>(lb + unit2(wn * 128 + 32 * i + xl, 2 * q + h)));
     }
   };
-  auto store = [&](int stage, int kvalid) {
-    uint16_t *la = lds + stage * 2 * OP2, *lb = la + OP2;
-    const bool dead = 8 * lg >= kvalid;   // K % 8 == 0
+  auto multiply = [&](int f) {
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      if (dead) ra[s] = rb[s] = make_uint4(0u, 0u, 0u, 0u);
-      *reinterpret_cast<uint4 *>(la + unit2(lr + 64 * s, lg)) = ra[s];
-      *reinterpret_cast<uint4 *>(lb + unit2(lr + 64 * s, lg)) = rb[s];
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[f][i], fb[f][j], acc[i][j], 0, 0, 0);
+  };
+  // One step's instructions in turn: two matrix instructions, an LDS read
+  // and (moves) an LDS write and a global load, eight times.
+  auto interleave = [&](auto moves) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      if constexpr (decltype(moves)::value) {
+        __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+      }
     }
+    __builtin_amdgcn_sched_barrier(0);
   };
   const int nk = (p.K + KB - 1) / KB;
-  if (nk > 0) {
-    load(0);
-    store(0, min(KB, p.K));
-  }
+  load(ra, pa, 0);
+  load(rb, pb, 0);
+  store(ra, op(0, 0), 0);
+  store(rb, op(0, 1), 0);
+  load(ra, pa, 1);
+  load(rb, pb, 1);
   __syncthreads();
+  frag(0, 0, 0);
   for (int kt = 0; kt < nk; ++kt) {
-    const bool more = kt + 1 < nk;
-    if (more) load((kt + 1) * KB);
-    const uint16_t *la = lds + (kt & 1) * 2 * OP2, *lb = la + OP2;
-#pragma unroll
-    for (int q = 0; q < KB / 16; ++q) {
-      v8bf fa[4], fb[2];
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-        fb[j] = __builtin_bit_cast(
-            v8bf, *reinterpret_cast<const uint4 *>(lb + unit2(wn * 64 + 32 * j + xl, 2 * q + h)));
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        fa[i] = __builtin_bit_cast(
-            v8bf, *reinterpret_cast<const uint4 *>(la + unit2(wm * 128 + 32 * i + xl, 2 * q + h)));
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
-    }
-    if (more) store((kt + 1) & 1, min(KB, p.K - (kt + 1) * KB));
+    __builtin_amdgcn_sched_barrier(0);
+    frag(1, kt, 1);
+    store(ra, op(kt + 1, 0), kt + 1);
+    load(ra, pa, kt + 2);
+    multiply(0);
+    interleave(std::true_type{});
+    frag(0, kt, 2);
+    store(rb, op(kt + 1, 1), kt + 1);
+    load(rb, pb, kt + 2);
+    multiply(1);
+    interleave(std::true_type{});
+    frag(1, kt, 3);
+    multiply(0);
+    interleave(std::false_type{});
     __syncthreads();
+    __builtin_amdgcn_sched_barrier(0);
+    frag(0, kt + 1, 0);
+    multiply(1);
+    interleave(std::false_type{});
   }
 
   uint16_t *C = p.C + bz * p.sC;
@@ -323,28 +360,40 @@ __global__ __launch_bounds__(NTH2, 2) void gemm_bf16_nt256(BfParams p) {
   uint16_t *Ct = MODE == BMODE_SYRK ? C : (p.Ct ? p.Ct + bz * p.sCt : nullptr);
   const int64_t ldct = MODE == BMODE_SYRK ? p.ldc : p.ldct;
   float *stage = reinterpret_cast<float *>(lds);
+  // thread -> (row (tid >> 5) + 8 u of a band, 8 columns)
+  const int er = tid >> 5, ec = 8 * (tid & 31);
+  uint4 dv[8];
+  auto load_d = [&](int ps) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int row = m0 + 64 * ps + er + 8 * u, col = n0 + ec;
+      dv[u] = make_uint4(0u, 0u, 0u, 0u);
+      if (D && row < p.M && col < p.N)                    // N % 8 == 0
+        dv[u] = *reinterpret_cast<const uint4 *>(D + (int64_t)row * p.ldd + col);
+    }
+  };
+  load_d(0);
+  __syncthreads();                         // the last fragments are read
 #pragma unroll
   for (int ps = 0; ps < 4; ++ps) {         // rows 64 ps .. 64 ps + 63 of the tile
     if (wm == ps >> 1) {
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < 4; ++j)
 #pragma unroll
           for (int r = 0; r < 16; ++r)
-            stage[(32 * i + 8 * (r >> 2) + 4 * h + (r & 3)) * SLD2 + wn * 64 + 32 * j + xl] =
+            stage[(32 * i + 8 * (r >> 2) + 4 * h + (r & 3)) * SLD2 + wn * 128 + 32 * j + xl] =
                 acc[2 * (ps & 1) + i][j][r];
     }
     __syncthreads();
     const int rb0 = m0 + 64 * ps;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {          // thread -> (row, 8 columns)
-      const int e = tid + NTH2 * u, row = rb0 + (e >> 5), c8 = 8 * (e & 31), col = n0 + c8;
-      float *sp = stage + (e >> 5) * SLD2 + c8;
+    for (int u = 0; u < 8; ++u) {
+      const int row = rb0 + er + 8 * u, col = n0 + ec;
+      float *sp = stage + (er + 8 * u) * SLD2 + ec;
       if (row >= p.M || col >= p.N) continue;             // N % 8 == 0
-      uint4 dv = make_uint4(0u, 0u, 0u, 0u);
-      if (D) dv = *reinterpret_cast<const uint4 *>(D + (int64_t)row * p.ldd + col);
-      const uint32_t dw[4] = {dv.x, dv.y, dv.z, dv.w};
+      const uint32_t dw[4] = {dv[u].x, dv[u].y, dv[u].z, dv[u].w};
       uint32_t ow[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
@@ -367,11 +416,12 @@ __global__ __launch_bounds__(NTH2, 2) void gemm_bf16_nt256(BfParams p) {
           if (col + q <= row) dst[q] = (uint16_t)(ow[q >> 1] >> (16 * (q & 1)));
       }
     }
+    if (ps < 3) load_d(ps + 1);
     __syncthreads();
     if (Ct) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {        // thread -> (column, 8 rows)
-        const int e = tid + NTH2 * u, c = e >> 3, r8 = 8 * (e & 7);
+      for (int u = 0; u < 8; ++u) {        // thread -> (column, 8 rows)
+        const int e = tid + NTH * u, c = e >> 3, r8 = 8 * (e & 7);
         const int col = n0 + c, row = rb0 + r8;
         if (col >= p.N || row >= p.M) continue;           // M % 8 == 0
         uint32_t ow[4];
@@ -437,10 +487,11 @@ __global__ __launch_bounds__(256) void axpby_bf16_kernel(float *__restrict__ W,
 
 }  // namespace
 
-// 256-tiles from half the compute units' count of them on: the iterations of
-// 4096 x 4096 (triangles of 136 tiles, 256 in the third product) take 6.94 ms
-// with them throughout and 7.77 when the triangles keep 128-tiles; 2048 x
-// 8192 (triangles of 36 tiles) 6.84 ms with and 4.62 without.  64-tiles while
+// 256-tiles from half the compute units' count of them on (figures of eight
+// waves per tile): the iterations of 4096 x 4096 (triangles of 136 tiles, 256
+// in the third product) take 6.94 ms with them throughout and 7.77 when the
+// triangles keep 128-tiles; 2048 x 8192 (triangles of 36 tiles) 6.84 ms with
+// and 4.62 without.  64-tiles while
 // 128-tiles would leave compute units idle: 1024 x 1024 1.64 -> 0.96 ms, 1536
 // x 3072 2.44 -> 1.95; a bound of 400 instead of 192 within 2% either way.
 static constexpr int64_t MIN_TILES_256 = 128;
@@ -472,8 +523,11 @@ hipError_t launch_gemm_bf16_nt(const BfGemmDesc &d, hipStream_t s) {
   tiles(T2);
   if (wide && d.K > 0 && p.ntiles * d.batch >= MIN_TILES_256 && !(d.syrk && d.Ct)) {
     const dim3 grid(p.ntiles, 1, (unsigned)d.batch);
-    if (d.syrk) hipLaunchKernelGGL(gemm_bf16_nt256<BMODE_SYRK>, grid, dim3(NTH2), 0, s, p);
-    else hipLaunchKernelGGL(gemm_bf16_nt256<BMODE_GENERAL>, grid, dim3(NTH2), 0, s, p);
+    const bool tail = p.K % KB != 0;
+#define SOAP_BF(MODE, TAIL) hipLaunchKernelGGL((gemm_bf16_nt256<MODE, TAIL>), grid, dim3(NTH), 0, s, p)
+    if (d.syrk) { if (tail) SOAP_BF(BMODE_SYRK, true); else SOAP_BF(BMODE_SYRK, false); }
+    else { if (tail) SOAP_BF(BMODE_GENERAL, true); else SOAP_BF(BMODE_GENERAL, false); }
+#undef SOAP_BF
   } else {
     tiles(128);
     const bool few = p.ntiles * d.batch <= MAX_TILES_64;
