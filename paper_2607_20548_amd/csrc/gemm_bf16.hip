@@ -49,10 +49,7 @@ struct BfParams {
 };
 
 __device__ __forceinline__ uint16_t to_bf16(float f) {   // nearest, ties to even
-  const uint32_t u = __float_as_uint(f);
-  if ((u & 0x7f800000u) == 0x7f800000u && (u & 0x007fffffu) != 0u)
-    return (uint16_t)((u >> 16) | 0x0040u);                  // NaN stays a (quiet) NaN
-  return (uint16_t)((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);
+  return __builtin_bit_cast(uint16_t, (__bf16)f);
 }
 __device__ __forceinline__ float from_bf16(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
@@ -222,27 +219,32 @@ __global__ __launch_bounds__(NTH, 2) void gemm_bf16_nt(BfParams p) {
 // and the slab's writes take three quarters of the matrix instructions'
 // time, where eight waves of 128 x 64 took all of it (12 KB).  K advances in
 // slabs of 64 through two LDS buffers of unpadded 128-byte rows whose 16-byte
-// units are permuted (unit g of row x at g ^ (x % 8)), so that eight
-// consecutive rows of one g cover all banks.  With one wave per SIMD nothing
-// else hides a latency, so each of a slab's four steps of 16 k multiplies
-// fragments read during the step before, the first two steps also move the
-// next slab from registers to LDS and load the one after it (in flight for a
-// whole slab), and the barrier lies before the fourth step, which reads the
-// next slab's first fragments.  The sums run over k in the same order as
-// with 128-tiles: the results are the same bit for bit.  Measured against
-// 128-tiles and eight waves of 128 x 64: B X of 4096 x 14336 750, 610 -> 518 us
-// (928 TFLOP/s; 3.5 tiles per CU, so 1060 while the chip is full); of 64 x (768
-// x 2048), K = 768, 665, 360 -> 324 us, most of it the epilogue's pass over
-// memory, which one tile per CU leaves uncovered.
+// units are permuted (unit g of row x at g ^ (x / 2 % 8)), so that sixteen
+// consecutive rows of one g lie in different banks (with x % 8 for x / 2 % 8,
+// which covers eight rows, conflicts took 0.4 of the LDS cycles: the step of
+// 4096 x 14336 15.3 -> 14.9 ms).  With one wave per SIMD nothing else hides a
+// latency, so each of a slab's four steps of 16 k multiplies fragments read
+// during the step before, the first two steps also move the next slab from
+// registers to LDS and load the one after it (in flight for a whole slab),
+// and the barrier lies before the fourth step, which reads the next slab's
+// first fragments.  The sums run over k in the same order as with 128-tiles:
+// the results are the same bit for bit.  Measured against 128-tiles and eight
+// waves of 128 x 64: B X of 4096 x 14336 750, 610 -> 500 us (960 TFLOP/s; 3.5
+// tiles per CU, so 1100 while the chip is full); of 64 x (768 x 2048), K = 768,
+// 665, 360 -> 300 us, most of it the epilogue, which one tile per CU leaves
+// uncovered (two tiles of 256 x 128 per CU took as long).  The matrix
+// instructions run 0.55-0.6 of the main loop's time; the rest is waiting for
+// memory.  A second slab in flight does not fit the registers.
 // Epilogue: 64 rows at a time through LDS in fp32 (each result is rounded
-// once), D read (a band ahead) and C written 16 bytes per lane, and the
-// transposed output (C itself mirrored in SYRK mode) from the columns of the
-// same 64 rows.
+// once, by the conversion instruction: in integer arithmetic the bank's step
+// took 10.4 ms instead of 9.8), D read (a band ahead) and C written 16 bytes
+// per lane, and the transposed output (C itself mirrored in SYRK mode) from
+// the columns of the same 64 rows.
 constexpr int T2 = 256;
 constexpr int OP2 = T2 * KB;                    // one operand slab, bfloat16 values
 constexpr int SLD2 = T2 + 4;                    // staging row in floats
 
-__device__ __forceinline__ int unit2(int x, int g) { return x * KB + 8 * (g ^ (x & 7)); }
+__device__ __forceinline__ int unit2(int x, int g) { return x * KB + 8 * (g ^ ((x >> 1) & 7)); }
 
 // TAIL: K is not a multiple of the slab.
 template <int MODE, bool TAIL>
@@ -267,25 +269,27 @@ __global__ __launch_bounds__(NTH, 1) void gemm_bf16_nt256(BfParams p) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-  // thread -> rows (tid >> 3) + 32 s, unit tid & 7 of each operand; slabs past
-  // the last are loaded from clamped addresses and never multiplied
+  // thread -> rows lr + 32 s, unit lg of each operand; slabs past the last
+  // are loaded from clamped addresses and never multiplied
   const int lr = tid >> 3, lg = tid & 7;
   uint4 ra[8], rb[8];
   const uint16_t *pa[8], *pb[8];
 #pragma unroll
-  for (int s = 0; s < 8; ++s) {
+  for (int s = 0; s < 8; ++s)
     pa[s] = P + (int64_t)min(m0 + lr + 32 * s, p.M - 1) * p.ldp;
+#pragma unroll
+  for (int s = 0; s < 8; ++s)
     pb[s] = Q + (int64_t)min(n0 + lr + 32 * s, p.N - 1) * p.ldq;
-  }
-  auto load = [&](uint4 (&r)[8], const uint16_t *const (&src)[8], int kt) {
+  auto load = [&](auto &r, const auto &src, int kt) {
     const int k = min(kt * KB + 8 * lg, p.K - 8);
 #pragma unroll
-    for (int s = 0; s < 8; ++s) r[s] = *reinterpret_cast<const uint4 *>(src[s] + k);
+    for (unsigned s = 0; s < sizeof(r) / sizeof(uint4); ++s)
+      r[s] = *reinterpret_cast<const uint4 *>(src[s] + k);
   };
-  auto store = [&](const uint4 (&r)[8], uint16_t *dst, int kt) {
+  auto store = [&](const auto &r, uint16_t *dst, int kt) {
     const bool dead = TAIL && kt * KB + 8 * lg >= p.K;   // K % 8 == 0
 #pragma unroll
-    for (int s = 0; s < 8; ++s)
+    for (unsigned s = 0; s < sizeof(r) / sizeof(uint4); ++s)
       *reinterpret_cast<uint4 *>(dst + unit2(lr + 32 * s, lg)) =
           dead ? make_uint4(0u, 0u, 0u, 0u) : r[s];
   };
@@ -295,10 +299,10 @@ __global__ __launch_bounds__(NTH, 1) void gemm_bf16_nt256(BfParams p) {
     const uint16_t *la = op(kt, 0), *lb = op(kt, 1);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      fa[f][i] = __builtin_bit_cast(
-          v8bf, *reinterpret_cast<const uint4 *>(la + unit2(wm * 128 + 32 * i + xl, 2 * q + h)));
-      fb[f][i] = __builtin_bit_cast(
-          v8bf, *reinterpret_cast<const uint4 *>(lb + unit2(wn * 128 + 32 * i + xl, 2 * q + h)));
+      fa[f][i] = __builtin_bit_cast(v8bf, *reinterpret_cast<const uint4 *>(
+          la + unit2(wm * 128 + 32 * i + xl, 2 * q + h)));
+      fb[f][i] = __builtin_bit_cast(v8bf, *reinterpret_cast<const uint4 *>(
+          lb + unit2(wn * 128 + 32 * i + xl, 2 * q + h)));
     }
   };
   auto multiply = [&](int f) {
@@ -308,8 +312,8 @@ __global__ __launch_bounds__(NTH, 1) void gemm_bf16_nt256(BfParams p) {
       for (int j = 0; j < 4; ++j)
         acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[f][i], fb[f][j], acc[i][j], 0, 0, 0);
   };
-  // One step's instructions in turn: two matrix instructions, an LDS read
-  // and (moves) an LDS write and a global load, eight times.
+  // One step's instructions in turn: two matrix instructions, an LDS read and
+  // (moves) an LDS write and a global load, eight times.
   auto interleave = [&](auto moves) {
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
