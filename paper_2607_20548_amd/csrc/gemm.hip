@@ -13,18 +13,20 @@
 // cut addends off below its last bits; as it is, the error against fp64 is
 // 2.2e-7 at 4096^3 and 3.1e-7 at 8192^3 (Gaussian operands), against 1.15e-6
 // and 1.6e-6 on v_mfma_f32_32x32x2_f32.  Operands are split once, on the way
-// to LDS.  Parts that would fall outside bfloat16's range are handled after the
-// K loop (see there).
-// Measured: 4096^3 1150 -> 850 us and 14336^3 (both operands x-contiguous)
-// 44.0 -> 35.2 ms against the fp32 instructions, i.e. 167-183 TFLOP/s
-// of products, 1.0-1.1 PFLOP/s of bfloat16 matrix work; the same launches on
-// zero operands run at 205-234, so that the card's power bounds the large
-// products (a large library product in bfloat16 runs at 1.37 PFLOP/s).
+// to LDS, scaled so that bfloat16's range holds their parts (see SCALE); sums
+// that overflow are handled after the K loop (see there).
+// Measured: 4096^3 1150 -> 870 us and 14336^3 (both operands x-contiguous)
+// 44.0 -> 37.7 ms against the fp32 instructions, i.e. 156-179 TFLOP/s
+// of products, 0.95-1.1 PFLOP/s of bfloat16 matrix work; the same launches on
+// zero operands ran at 205-234, so that the card's power bounds the large
+// products (a large library product in bfloat16 runs at 1.37 PFLOP/s).  The
+// scaling is one multiplication per loaded value (850 and 35.6 without).
 //
 // Tiling: a 256-thread workgroup (4 wave64s in a 2 x 2 arrangement) computes a
 // 128 x 128 tile of C (64 x 64 for products with few tiles); each wave owns a
-// 64 x 64 sub-tile held as 2 x 2 32x32 accumulators.  K advances in slabs of 32; the global loads of the next slab
-// are in flight while a slab is multiplied.
+// 64 x 64 sub-tile held as 2 x 2 32x32 accumulators.  K advances in slabs of
+// 32; the global loads of the next slab are in flight while a slab is
+// multiplied.
 //
 // Epilogue: the tile goes through LDS (free after the K loop) so that C is read
 // and written 16 bytes per lane (see the epilogue).
@@ -66,8 +68,14 @@ struct Lds {
   }
 };
 
-// Sums below this (2^-90, as bits) are taken again in fp32.
-constexpr uint32_t EXACT_BELOW = (127u - 90u) << 23;
+// Operands are scaled by this on their way to the parts and the sums scaled
+// back at the end (both exact short of fp32's own range): the last bit of the
+// smallest fp32 value, 2^-149, becomes 2^-133, the smallest bfloat16, so that
+// the three parts hold every operand exactly (the matrix instructions keep
+// bfloat16's subnormals).  Unscaled, operands below 2^-110 lost bits: 1e-37
+// times 1e12 came out with a relative error of 3e-4.
+constexpr float SCALE = 65536.f;
+constexpr float UNSCALE = 1.f / (SCALE * SCALE);
 
 enum { MODE_GENERAL = 0, MODE_SYRK = 1, MODE_ADAM = 2 };
 // How an operand is read: V_ALIGNED with 16-byte (k-contiguous) or 8-byte
@@ -99,11 +107,13 @@ struct KParams {
 struct f4u { float x, y, z, w; };   // 4-byte aligned
 struct f2u { float x, y; };
 
-// Two floats as three bfloat16 pairs with x = hi + mid + lo exactly (for
-// |x| from about 2^-102 to the largest bfloat16): each part is the remainder
-// rounded to nearest, so mid <= 2^-9 |x| and lo <= 2^-18 |x|.
+// Two floats as three bfloat16 pairs with SCALE x = hi + mid + lo exactly
+// (for |x| below 2^111, past which a part is infinite): each part is the
+// remainder rounded to nearest, so mid <= 2^-9 hi and lo <= 2^-18 hi.
 __device__ __forceinline__ void split2(float x0, float x1, uint32_t &hi, uint32_t &mid,
                                        uint32_t &lo) {
+  x0 *= SCALE;
+  x1 *= SCALE;
   const v2f v = {x0, x1};
   hi = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, v2bf));
   const float r0 = x0 - __uint_as_float(hi << 16);
@@ -360,10 +370,10 @@ __global__ __launch_bounds__(NTHREADS, BT == BIG ? 2 : 3) void gemm_f32_split(KP
   }
 
   // A wave whose sums hold an infinity or a NaN (an infinite operand times a
-  // zero part gives NaN here and not in fp32; so does an operand that
-  // rounds past the largest bfloat16), or whose largest sum is so small that
-  // parts of the operands fell below the smallest bfloat16, takes its sums
-  // again on the fp32 matrix instructions, straight from memory.
+  // zero part gives NaN here and not in fp32; operands from 2^111 and sums
+  // from 2^96 on overflow by their scale) takes its sums again on the fp32
+  // matrix instructions, straight from memory (4096^3 of NaN: 2.7-4.0 ms, 35
+  // to 51 TFLOP/s); the others are scaled back.
   {
     uint32_t mx = 0u;
 #pragma unroll
@@ -371,33 +381,44 @@ __global__ __launch_bounds__(NTHREADS, BT == BIG ? 2 : 3) void gemm_f32_split(KP
 #pragma unroll
       for (int j = 0; j < NBLK; ++j)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) mx = max(mx, __float_as_uint(acc[i][j][r]) & 0x7fffffffu);
-    const bool big = __any(mx >= 0x7f800000u);
-    const bool tiny = __any(mx != 0u) && !__any(mx >= EXACT_BELOW);
-    if (big || tiny) {
+        for (int r = 0; r < 16; ++r) {
+          mx = max(mx, __float_as_uint(acc[i][j][r]) & 0x7fffffffu);
+          acc[i][j][r] *= UNSCALE;
+        }
+    if (__any(mx >= 0x7f800000u)) {
 #pragma unroll
       for (int i = 0; i < NBLK; ++i)
 #pragma unroll
         for (int j = 0; j < NBLK; ++j)
 #pragma unroll
           for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+      constexpr int U = 4;   // pairs of k in flight
 #pragma unroll 1
-      for (int k = kbeg; k < kend; k += 2) {
-        const int kk = min(k + h, kend - 1);
-        const float live = (k + h < kend) ? 1.f : 0.f;
-        float ea[NBLK], eb[NBLK];
+      for (int k = kbeg; k < kend; k += 2 * U) {
+        float ea[U][NBLK], eb[U][NBLK];
 #pragma unroll
-        for (int i = 0; i < NBLK; ++i) {
-          const float va = operand_at<TA == 0>(A, p.lda, m0 + wm * WT + 32 * i + xl, kk, p.M);
-          const float vb = operand_at<TB == 1>(B, p.ldb, n0 + wn * WT + 32 * i + xl, kk, p.N);
-          ea[i] = live != 0.f ? va : 0.f;
-          eb[i] = live != 0.f ? vb : 0.f;
+        for (int u = 0; u < U; ++u) {
+          const int kk = min(k + 2 * u + h, kend - 1);
+#pragma unroll
+          for (int i = 0; i < NBLK; ++i) {
+            ea[u][i] = operand_at<TA == 0>(A, p.lda, m0 + wm * WT + 32 * i + xl, kk, p.M);
+            eb[u][i] = operand_at<TB == 1>(B, p.ldb, n0 + wn * WT + 32 * i + xl, kk, p.N);
+          }
         }
 #pragma unroll
-        for (int i = 0; i < NBLK; ++i)
+        for (int u = 0; u < U; ++u) {
+          const bool live = k + 2 * u + h < kend;
 #pragma unroll
-          for (int j = 0; j < NBLK; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(ea[i], eb[j], acc[i][j], 0, 0, 0);
+          for (int i = 0; i < NBLK; ++i) {
+            ea[u][i] = live ? ea[u][i] : 0.f;
+            eb[u][i] = live ? eb[u][i] : 0.f;
+          }
+#pragma unroll
+          for (int i = 0; i < NBLK; ++i)
+#pragma unroll
+            for (int j = 0; j < NBLK; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(ea[u][i], eb[u][j], acc[i][j], 0, 0, 0);
+        }
       }
     }
   }

@@ -68,7 +68,7 @@ def test_layouts_edges_and_alignment(soap, ta, tb, M, N, K, pad, shift):
 
 @pytest.mark.parametrize("scale", [1e-30, 1e-34, 1e-37])
 def test_tiny_operands(soap, scale):
-    """Parts below the smallest bfloat16: as exact as any other product."""
+    """Every element of one operand tiny, the other of order one."""
     import torch
     A, pa, lda, ah = operand(140, 96, 0, 0, 1, scale)
     B, pb, ldb, bh = operand(96, 130, 0, 0, 2)
@@ -77,6 +77,45 @@ def test_tiny_operands(soap, scale):
     want = ah @ bh
     got = C.cpu().numpy().astype(np.float64)
     assert np.linalg.norm(got - want) / np.linalg.norm(want) <= bound(96)
+
+
+@pytest.mark.parametrize("ta", [0, 1])
+@pytest.mark.parametrize("tb", [0, 1])
+@pytest.mark.parametrize("M,N,K", [(140, 130, 96), (1801, 2051, 65)])
+def test_small_operands_beside_ordinary_ones(soap, ta, tb, M, N, K):
+    """Rows of A from 1 down to fp32's subnormals, columns of B from 1 up to
+    1e20, all in the same tiles: every element of the product is as exact as
+    one of ordinary operands (relative to its own sum of |a||b|; a result
+    below fp32's normal range may also be rounded to its last bit)."""
+    import torch
+    rng = np.random.default_rng(4)
+    rows = np.array([1.0, 1e-36, 1e-30, 1e-38, 1e-41])[np.arange(M) % 5]
+    cols = np.array([1.0, 1e10, 1e20])[np.arange(N) % 3]
+    a = (rng.standard_normal((M, K)) * rows[:, None]).astype(np.float32)
+    b = (rng.standard_normal((K, N)) * cols[None, :]).astype(np.float32)
+    A = torch.from_numpy(np.ascontiguousarray(a.T if ta else a)).cuda()
+    B = torch.from_numpy(np.ascontiguousarray(b.T if tb else b)).cuda()
+    C = torch.empty(M, N, device="cuda")
+    soap.soap_gemm_f32(ta, tb, M, N, K, 1.0, A, A.shape[1], B, B.shape[1], 0.0, C, N)
+    a64, b64 = a.astype(np.float64), b.astype(np.float64)
+    err = np.abs(C.cpu().numpy().astype(np.float64) - a64 @ b64)
+    limit = (-(-K // 32) + 12) * 2.0 ** -23 * (np.abs(a64) @ np.abs(b64)) + 2.0 ** -149
+    assert (err <= limit).all(), float((err / limit).max())
+
+
+def test_sums_past_the_scaled_range(soap):
+    """Sums near 1e30 and 1e36 (finite, but not when scaled): taken on the fp32
+    instructions, odd K included."""
+    import torch
+    for scale in (1e15, 1e18):
+        A, pa, lda, ah = operand(140, 77, 0, 0, 1, scale)
+        B, pb, ldb, bh = operand(77, 130, 0, 0, 2, scale)
+        C = torch.empty(140, 130, device="cuda")
+        soap.soap_gemm_f32(0, 0, 140, 130, 77, 1.0, pa, lda, pb, ldb, 0.0, C, 130)
+        want = ah @ bh
+        got = C.cpu().numpy().astype(np.float64)
+        # fp32 accumulation in order: sqrt(K) roundings of 2^-24, four times that
+        assert np.linalg.norm(got - want) / np.linalg.norm(want) <= 4 * 2.0 ** -24 * 77 ** 0.5
 
 
 def test_infinite_and_huge_operands(soap):
