@@ -554,36 +554,45 @@ constexpr int BK_KMAX = 8;                      // columns per round at most
 // rows j.. before them): the sums that give its reflector would lose digits
 // to cancellation.
 constexpr float BK_TAU = 0.0625f;
-// Exchange area per matrix, in 32-bit words: a header (the abort flag, the
-// failed flag, and per slot area the words written there since it was last
-// emptied), then two slot areas that the outer blocks use in turn.  A round
-// of a block with P workgroups has a slot of its own, bk_col_words(P) items
-// of NB columns each: [BK_KMAX][P] partials of the dots (pivot i, workgroup g
-// is item i * P + g), then the BK_KMAX values of workgroup 0 in the diagonal
-// rows; item e of column k at word e * NB + (k mod 8) * 16 + k / 8 (the
-// columns of one wave are adjacent, so that one load by a wave touches few
-// cache lines).  Every word is written at most once between two
+// Exchange memory, in 32-bit words: a header per matrix (the abort flag, the
+// failed flag, and per slot area the words the matrix last wrote there), then
+// two slot areas that the block launches use in turn, each for the matrices
+// of its launch only: matrix i of a launch of P > 1 workgroups per matrix at
+// word i * bk_pos_words(P).  A round has a slot of its own, bk_col_words(P)
+// items of NB columns each: [BK_KMAX][P] partials of the dots (pivot i,
+// workgroup g is item i * P + g), then the BK_KMAX values of workgroup 0 in
+// the diagonal rows; item e of column k at word e * NB + (k mod 8) * 16 +
+// k / 8 (the columns of one wave are adjacent, so that one load by a wave
+// touches few cache lines).  Every word is written at most once between two
 // emptyings, over the empty pattern BK_EMPTY (a NaN that no post carries:
 // posted NaNs are canonical), so a reader knows a value has arrived from its
-// bits alone.  A block kernel empties, after its rounds, what the previous
-// block wrote into the area that the next block uses.
+// bits alone.  A block kernel empties, after its rounds, what the launch
+// before it wrote into the area that the next one uses (all of a matrix's
+// slots if its exchange was aborted: what was posted then is not known).
+// Launches of one workgroup per matrix exchange nothing and use no slots; once
+// P is 1, it stays 1.
 constexpr int64_t BK_XABORT = 0;
 constexpr int64_t BK_XFAILED = 1;
 constexpr int64_t BK_XUSED = 2;                 // words 2, 3: written words of area 0, 1
 constexpr int64_t BK_XHDR = 64;
 constexpr unsigned BK_EMPTY = 0xFFFFFFFFu;
-// Workgroups of the widest block launch for order n (the big-R kernel at
-// block 0, or the small-R kernel where it is taken).
-constexpr int64_t bk_max_p(int64_t n) {
-  const int64_t big = (n + BK_ROWS - 1) / BK_ROWS;
-  const int64_t sm = (n + BK_ROWS_SMALL - 1) / BK_ROWS_SMALL;
-  const int64_t s2 = sm < BK_SMALL_MAX_P ? sm : BK_SMALL_MAX_P;
-  return big > s2 ? big : s2;
-}
 __host__ __device__ constexpr int64_t bk_col_words(int64_t P) { return BK_KMAX * P + BK_KMAX; }
-// words of one slot area: at most NB rounds per block
-constexpr int64_t bk_area_words(int64_t n) { return (int64_t)NB * NB * bk_col_words(bk_max_p(n)); }
-constexpr int64_t bk_xstride(int64_t n) { return BK_XHDR + 2 * bk_area_words(n); }
+// slots of one matrix of a launch: at most NB rounds per block
+constexpr int64_t bk_pos_words(int64_t P) { return P > 1 ? (int64_t)NB * NB * bk_col_words(P) : 0; }
+// Words of one slot area: the most that any block's launch may need, with
+// either kernel (at most BK_MAX_WG workgroups per launch, so that batches
+// share about what one matrix of BK_MAX_WG workgroups would take).
+int64_t bk_area_words(int64_t batch, int64_t n) {
+  int64_t words = 0;
+  for (int64_t rows = n; rows > 0; rows -= NB) {
+    const int64_t big = (rows + BK_ROWS - 1) / BK_ROWS;
+    const int64_t sm = (rows + BK_ROWS_SMALL - 1) / BK_ROWS_SMALL;
+    for (const int64_t P : {big, sm <= BK_SMALL_MAX_P ? sm : big})
+      words = std::max(words, std::min<int64_t>(batch, std::max<int64_t>(1, BK_MAX_WG / P)) *
+                                  bk_pos_words(P));
+  }
+  return words;
+}
 
 struct BlockParams {
   float *At;
@@ -593,9 +602,16 @@ struct BlockParams {
   int64_t sT;
   float *Rf;                 // optional triangular-factor output (batch stride sA)
   float *dsign, *beta;       // n per matrix
-  unsigned *xch;             // exchange area, xstride words per matrix
-  int64_t xstride, area_words;
-  int area;                  // slot area of this block (0 or 1)
+  unsigned *hdr;             // header of the launch's first matrix
+  unsigned *slots;           // slot area of this launch, pos_words per matrix
+  int64_t pos_words;
+  int area;                  // ... which of the two (0 or 1)
+  // what to empty in the other one: prev_words words of each of prev_n
+  // matrices, as far as prev_hdr's headers say they were written (nullptr: all)
+  const unsigned *prev_hdr;
+  unsigned *prev_slots;
+  int64_t prev_words;
+  int prev_n;
   int P;                     // workgroups per matrix
   unsigned *status;          // caller's status word (or nullptr) ...
   unsigned status_bit;       // ... and the bit a give-up or-s into it
@@ -795,9 +811,9 @@ __global__ __launch_bounds__(BK_THREADS) void qr_block_kernel(BlockParams p) {
   const int r0 = c + g * RS;
   const bool w0 = (g == 0);
   const bool col = k < nb;
-  unsigned *X = p.xch + bz * p.xstride;
+  unsigned *X = p.hdr + bz * BK_XHDR;
   unsigned *abort_flag = X + BK_XABORT;
-  unsigned *slots = X + BK_XHDR + p.area * p.area_words;   // this block's rounds
+  unsigned *slots = p.slots + bz * p.pos_words;            // this block's rounds
   const int64_t cw = (int64_t)KM * P + KM;          // items per column and round
   const int64_t pk = (int64_t)(wave * (64 / BK_PARTS) + lane / BK_PARTS);   // position of column k
   const int lbase = lane & ~(BK_PARTS - 1);
@@ -1348,19 +1364,33 @@ __global__ __launch_bounds__(BK_THREADS) void qr_block_kernel(BlockParams p) {
         }
       }
   }
-  {
-    // The words this block wrote, for the emptying after the next block;
-    // then what the previous block wrote into the other area (which the next
-    // block uses) back to the empty pattern.
+  if (P > 1) {
+    // The words this matrix wrote, for the emptying by the next launch; then
+    // what the launch before wrote into the other area (which the next one
+    // uses) back to the empty pattern.
     if (w0 && t == 0)
-      __hip_atomic_store(X + BK_XUSED + p.area, P > 1 ? (unsigned)(round * NB * cw) : 0u,
-                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const int64_t used = (int64_t)__hip_atomic_load(X + BK_XUSED + (1 - p.area), __ATOMIC_RELAXED,
-                                                    __HIP_MEMORY_SCOPE_AGENT);
-    uint4 *nx = reinterpret_cast<uint4 *>(X + BK_XHDR + (1 - p.area) * p.area_words);
+      __hip_atomic_store(X + BK_XUSED + p.area, (unsigned)(round * NB * cw), __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
     const uint4 e4 = make_uint4(BK_EMPTY, BK_EMPTY, BK_EMPTY, BK_EMPTY);
-    for (int64_t i = (int64_t)g * BK_THREADS + t; i < used / 4; i += (int64_t)P * BK_THREADS)
-      nx[i] = e4;
+    if (!p.prev_hdr) {
+      const int64_t words = p.prev_n * p.prev_words;
+      uint4 *nx = reinterpret_cast<uint4 *>(p.prev_slots);
+      for (int64_t i = (bz * P + g) * BK_THREADS + t; i < words / 4;
+           i += (int64_t)gridDim.y * P * BK_THREADS)
+        nx[i] = e4;
+    } else {
+      for (int64_t q = bz; q < p.prev_n; q += gridDim.y) {
+        const unsigned *h = p.prev_hdr + q * BK_XHDR;
+        const int64_t words =
+            __hip_atomic_load(h + BK_XABORT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u
+                ? p.prev_words
+                : (int64_t)__hip_atomic_load(h + BK_XUSED + (1 - p.area), __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT);
+        uint4 *nx = reinterpret_cast<uint4 *>(p.prev_slots + q * p.prev_words);
+        for (int64_t i = (int64_t)g * BK_THREADS + t; i < words / 4; i += (int64_t)P * BK_THREADS)
+          nx[i] = e4;
+      }
+    }
   }
   if (!w0) return;
   // T by blocks of 8 columns: first every diagonal block T_JJ (rows of one
@@ -1653,24 +1683,22 @@ __global__ __launch_bounds__(256) void qr_q_head_kernel(float *W, int64_t ldw, i
   }
 }
 
-// Raises the abort flag of each of `batch` exchange areas (the forced
-// give-up of qr_force_give_up).
-__global__ __launch_bounds__(64) void qr_raise_abort_kernel(unsigned *xch, int64_t xstride,
-                                                            int64_t batch) {
+// Raises the abort flags of `batch` headers (the forced give-up of
+// qr_force_give_up).
+__global__ __launch_bounds__(64) void qr_raise_abort_kernel(unsigned *hdr, int64_t batch) {
   for (int64_t b = blockIdx.x * 64 + threadIdx.x; b < batch; b += (int64_t)gridDim.x * 64)
-    __hip_atomic_store(xch + b * xstride + BK_XABORT, 1u, __ATOMIC_RELAXED,
+    __hip_atomic_store(hdr + b * BK_XHDR + BK_XABORT, 1u, __ATOMIC_RELAXED,
                        __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Exchange areas at the start of a call: header words zero, area 0 (the
-// first block's) empty, and area 1 marked as written throughout, so that the
-// first block empties all of it for the second.
-__global__ __launch_bounds__(256) void qr_xch_init_kernel(unsigned *xch, int64_t xstride,
+// Exchange memory at the start of a call: header words zero, area 0 (the
+// first launch's, right after them) empty; the first launch empties area 1
+// for the second.
+__global__ __launch_bounds__(256) void qr_xch_init_kernel(unsigned *xch, int64_t hdr_words,
                                                           int64_t area_words) {
-  unsigned *X = xch + (int64_t)blockIdx.y * xstride;
-  const int64_t cnt = BK_XHDR + area_words;
-  for (int64_t i = blockIdx.x * 256 + threadIdx.x; i < cnt; i += (int64_t)gridDim.x * 256)
-    X[i] = (i < BK_XHDR) ? (i == BK_XUSED + 1 ? (unsigned)area_words : 0u) : BK_EMPTY;
+  for (int64_t i = blockIdx.x * 256 + threadIdx.x; i < hdr_words + area_words;
+       i += (int64_t)gridDim.x * 256)
+    xch[i] = i < hdr_words ? 0u : BK_EMPTY;
 }
 
 // dst = src^T for one n x n matrix, through 32 x 32 LDS tiles.
@@ -1697,6 +1725,7 @@ struct QrLayout {
   size_t tp_off, sx_off, skp_off, skp2_off, tq_off, sq_off, to_off, so_off, wn_off, skn_off;
   size_t fv_off;
   int64_t sT, sWbuf, sSk, sPart, sWi;
+  int64_t area;        // words of one slot area of the exchange
   int64_t sFv;         // the forward Q formation's V = Q Y and V T (n x 2 NB each)
   int64_t sWn, sSkn;   // the near update's own W, W2 (NB x NB each) and split-K partials
   int64_t np;          // pairs of full outer blocks
@@ -1769,7 +1798,8 @@ QrLayout qr_layout(int64_t batch, int64_t n) {
   const int64_t P0 = (n + BK_ROWS - 1) / BK_ROWS;
   L.block = P0 <= BK_MAX_P && P0 <= BK_MAX_WG;
   L.x_off = o;
-  if (L.block) o = align256(o + sizeof(unsigned) * batch * bk_xstride(n));
+  L.area = bk_area_words(batch, n);
+  if (L.block) o = align256(o + sizeof(unsigned) * (batch * BK_XHDR + 2 * L.area));
   L.total = o;
   return L;
 }
@@ -1843,6 +1873,14 @@ struct QrCtx {
   float *Tb, *Wb, *W2, *Sk, *Pt, *Wi, *dsign, *betas;
   unsigned *cnt;
   unsigned *xch;
+  // The block launches' use of the two slot areas so far: launches that have
+  // exchanged, and what the last of them wrote (as in BlockParams).
+  struct Turns {
+    int64_t done = 0, total = 0;
+    const unsigned *hdr = nullptr;
+    int64_t words = 0;
+    int n = 0;
+  } *turns;
   float *TP, *Sx, *Skp, *TQ, *Sq, *TO, *So;
   float *Wn, *Skn;
   float *Skp2;     // split-K partials of the pair T's (the merges use Skp)
@@ -1861,19 +1899,30 @@ int narrow_split(int64_t M, int64_t N, int64_t K, int64_t batch, int64_t cap_flo
   return (int)std::max<int64_t>(1, s);
 }
 
-// Workgroups per matrix of block ob's resident-block launch and whether it
-// takes the small-R kernel (whose launches hold the whole batch).
-int block_launch_p(const QrCtx &x, int64_t ob, bool *small) {
-  const int64_t c = ob * NB;
-  const int Ps = (int)((x.n - c + BK_ROWS_SMALL - 1) / BK_ROWS_SMALL);
-  *small = Ps == 1 || (Ps <= BK_SMALL_MAX_P && Ps * x.batch <= x.cap_small);
-  return *small ? Ps : (int)((x.n - c + BK_ROWS - 1) / BK_ROWS);
+// Block ob's launches: workgroups per matrix, whether they take the small-R
+// kernel (whose launches hold the whole batch), their number and the matrices
+// of each but the last (of equal size).
+struct BlockPlan {
+  int P;
+  bool small;
+  int64_t launches, step;
+};
+BlockPlan block_plan(const QrCtx &x, int64_t ob) {
+  BlockPlan b;
+  const int64_t rows = x.n - ob * NB;
+  const int Ps = (int)((rows + BK_ROWS_SMALL - 1) / BK_ROWS_SMALL);
+  b.small = Ps == 1 || (Ps <= BK_SMALL_MAX_P && Ps * x.batch <= x.cap_small);
+  b.P = b.small ? Ps : (int)((rows + BK_ROWS - 1) / BK_ROWS);
+  const int64_t per = b.P == 1 ? x.batch : std::max<int64_t>(1, x.cap_big / b.P);
+  b.launches = (x.batch + per - 1) / per;
+  b.step = (x.batch + b.launches - 1) / b.launches;
+  return b;
 }
 
 // Factors outer block ob on stream s (resident-block kernel or panel path).
 // A batch whose workgroups cannot all be resident takes several launches in
 // turn, each over as many matrices as can be (any number when a matrix is
-// one workgroup, which waits for nobody).  On 64 x (2048 x 768) the panel path
+// one workgroup, which waits for nobody), which share the exchange's slots.  On 64 x (2048 x 768) the panel path
 // takes 62 ms of panel kernels per step (one workgroup per matrix and panel,
 // 176 panels), these launches 22 ms: the step 78.0 -> 51.8 ms (64 x 1024^2
 // 37.6 -> 19.5 with the faster products, 512 x 128^2 7.2 -> 1.7).  Up to 128
@@ -1882,19 +1931,31 @@ hipError_t factor_block(const QrCtx &x, int64_t ob, hipStream_t s) {
   if (!x.L.block) return panel_phase(x, ob, s);
   const int c = (int)(ob * NB);
   const int nb = (int)std::min<int64_t>(NB, x.n - c);
-  bool small = false;
-  const int P = block_launch_p(x, ob, &small);
-  const int64_t xs = bk_xstride(x.n);
-  const int64_t per = P == 1 ? x.batch : std::max<int64_t>(1, x.cap_big / P);
-  const int64_t launches = (x.batch + per - 1) / per;
-  const int64_t step = (x.batch + launches - 1) / launches;   // of equal size
-  for (int64_t b0 = 0; b0 < x.batch; b0 += step) {
+  const BlockPlan b = block_plan(x, ob);
+  const int P = b.P;
+  const int64_t pos = bk_pos_words(P);
+  unsigned *areas = x.xch + x.batch * BK_XHDR;
+  QrCtx::Turns &t = *x.turns;
+  for (int64_t b0 = 0; b0 < x.batch; b0 += b.step) {
+    const int cnt = (int)std::min(b.step, x.batch - b0);
+    unsigned *hdr = x.xch + b0 * BK_XHDR;
+    const int area = (int)(t.done & 1);
     BlockParams bp{x.At + b0 * x.sA, x.sA, x.ni, c, nb, x.Tb + b0 * x.L.sT + ob * NB * NB, x.L.sT,
                    x.Rf ? x.Rf + b0 * x.sA : nullptr, x.dsign + b0 * x.n, x.betas + b0 * x.n,
-                   x.xch + b0 * xs, xs, bk_area_words(x.n), (int)(ob & 1), P, x.status,
-                   x.status_bit};
-    const dim3 grid((unsigned)P, (unsigned)std::min(step, x.batch - b0));
-    if (small)
+                   hdr, areas + area * x.L.area, pos, area,
+                   t.hdr, areas + (1 - area) * x.L.area, t.words, t.n, P, x.status, x.status_bit};
+    if (P > 1) {
+      if (t.done == 0) {   // area 1 as a whole, if a launch will use it
+        bp.prev_words = x.L.area;
+        bp.prev_n = t.total > 1 ? 1 : 0;
+      }
+      ++t.done;
+      t.hdr = hdr;
+      t.words = pos;
+      t.n = cnt;
+    }
+    const dim3 grid((unsigned)P, (unsigned)cnt);
+    if (b.small)
       hipLaunchKernelGGL((qr_block_kernel<BK_R_SMALL, BK_K_SMALL>), grid, dim3(BK_THREADS), 0, s,
                          bp);
     else if (P <= BK_MID_MAX_P)
@@ -2326,21 +2387,26 @@ hipError_t qr_factor_and_form_q(float *At, float *Q, float *Rf, int64_t batch, i
   SOAP_TRY(launch_zero_u32(x.cnt, batch, s));
   x.skip = nullptr;
   x.sSkip = 0;
-  if (x.L.block) {  // header clear, area 0 empty, area 1 emptied by the first block
-    const int64_t xs = bk_xstride(n), aw = bk_area_words(n);
-    const unsigned gx = (unsigned)std::min<int64_t>((BK_XHDR + aw + 255) / 256, 1024);
-    hipLaunchKernelGGL(qr_xch_init_kernel, dim3(gx, (unsigned)batch), dim3(256), 0, s, x.xch, xs,
-                       aw);
+  QrCtx::Turns turns;
+  x.turns = &turns;
+  if (x.L.block) {
+    for (int64_t ob = 0; ob < nob; ++ob) {
+      const BlockPlan b = block_plan(x, ob);
+      if (b.P > 1) turns.total += b.launches;
+    }
+    const int64_t hw = batch * BK_XHDR, aw = turns.total > 0 ? x.L.area : 0;
+    const unsigned gx = (unsigned)std::min<int64_t>((hw + aw + 255) / 256, 4096);
+    hipLaunchKernelGGL(qr_xch_init_kernel, dim3(gx), dim3(256), 0, s, x.xch, hw, aw);
     SOAP_TRY(hipGetLastError());
     x.skip = x.xch + BK_XFAILED;
-    x.sSkip = xs;
+    x.sSkip = BK_XHDR;
     for (int h = 0; h < (split ? 2 : 1); ++h) {
       const unsigned bit = split ? (h ? split->bitB : split->bitA) : status_bit;
       const int64_t cnt = split ? split->half : batch;
       if (g_force_give_up.load() & bit) {
         hipLaunchKernelGGL(qr_raise_abort_kernel,
                            dim3((unsigned)std::min<int64_t>((cnt + 63) / 64, 1024)), dim3(64), 0,
-                           s, x.xch + h * cnt * xs, xs, cnt);
+                           s, x.xch + h * cnt * BK_XHDR, cnt);
         SOAP_TRY(hipGetLastError());
       }
     }

@@ -229,6 +229,20 @@ def test_status_and_diagnostic_entry_points_validate(L):
     assert soap.soap_qr_workspace_bytes(64) > 4 * 64 * 64
 
 
+def test_batches_share_the_exchange_slots():
+    """The QR's exchange slots belong to the matrices of one launch: a further
+    matrix of a batch past that adds none (at least 8 (P + 1) NB^2 words per
+    side of P > 1 workgroups, twice), and matrices of one workgroup (orders up
+    to 128) have none at all."""
+    slots = lambda P: 2 * 4 * 128 * 128 * 8 * (P + 1)  # noqa: E731
+    for m, n, P in [(2048, 768, 8 + 3), (1024, 1024, 4 + 4), (300, 300, 2 + 2)]:
+        one = soap.soap_workspace_bytes(1, m, n)
+        more = (soap.soap_workspace_bytes(232, m, n) - soap.soap_workspace_bytes(200, m, n)) / 32
+        assert more + slots(P) <= one, (m, n)
+    assert soap.soap_workspace_bytes(512, 128, 128) <= 512 * soap.soap_workspace_bytes(1, 128, 128)
+    assert soap.soap_workspace_bytes(1, 128, 128) + slots(1) <= soap.soap_workspace_bytes(1, 129, 129)
+
+
 def test_noalloc_step_validates_before_touching_the_device(L):
     a = fake_args()
     args = lambda **o: [dict(a, **o)[k] for k in ("param", "grad", "L", "R", "Q_L", "Q_R", "M", "V")]
