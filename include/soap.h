@@ -233,7 +233,10 @@ const char *soap_last_error(void);
  * WAS ON ENTRY, and the rest of the step runs with it, exactly as a step with
  * SOAP_FLAG_SKIP_REFRESH would for that side.  The step sets the bit of that
  * side in the status word at offset 0 of its workspace; every step clears the
- * word when it starts.
+ * word when it starts.  Batches that take several launches per block (more
+ * than 96 workgroups of 256 rows each on a side) never give up: their waits
+ * are short, and a block whose wait ends without its partners is factored
+ * again by one workgroup that waits for nobody.
  *
  * This call waits for `stream` (a host synchronisation), reads the word into
  * *status (if not NULL) and returns SOAP_OK when it is 0, SOAP_ERR_QR_GAVE_UP
@@ -252,7 +255,8 @@ size_t soap_workspace_update_offset(int64_t batch, int64_t m, int64_t n);
  * soap_qr_f32) whose SOAP_STATUS_QR_* bit is in `mask` starts with the abort
  * flags of its resident block factorizations raised, so that each of their
  * bounded waits gives up at once and every kernel still exits normally: the
- * give-up path above, on demand.  mask = 0 restores normal operation.  Only
+ * give-up path above, on demand (in batches of several launches per block,
+ * the repair of every block).  mask = 0 restores normal operation.  Only
  * QRs that take the resident block path are affected (matrices whose
  * factorization runs in more than one workgroup per block).  Returns
  * SOAP_ERR_HPARAM for other bits. */

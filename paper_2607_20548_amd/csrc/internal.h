@@ -180,7 +180,10 @@ hipError_t launch_axpby_bf16(float *W, const uint16_t *X, int64_t count, float a
 // be resident, e.g. because other work held the compute units), the matrix's
 // factorization is marked failed: `status_bit` is or-ed into *status (if
 // status is not null), and Q (and Rf) of that matrix are left as they were
-// on entry -- the Q formation is skipped for it.  qr_force_give_up(mask)
+// on entry -- the Q formation is skipped for it.  (In batches that take several
+// launches per block the failed matrix's block is factored again instead, by
+// one workgroup, and nothing is reported; Rf must be null for these.)
+// qr_force_give_up(mask)
 // makes every later call whose status_bit is in `mask` start with its
 // matrices' abort flags raised (a test hook: every bounded wait then ends at
 // once and the kernels exit normally).

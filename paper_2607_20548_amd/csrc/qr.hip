@@ -530,6 +530,12 @@ __global__ __launch_bounds__(256) void qr_inner_apply_kernel(ApplyParams p) {
 // saw the abort marks the matrix's factorization failed (the Q formation
 // then leaves that matrix's Q as it was) and or-s the caller's status bit
 // into its status word.
+// Batches of several launches per block (more than BK_MAX_WG workgroups) do
+// not fail: each launch keeps a copy of the block as it was, waits only for
+// BK_SPIN_REPAIR polls (some 50 ms), and qr_repair_block_kernel, which waits
+// for nobody, then factors the blocks of failed matrices again.  Two such
+// steps on two streams ask for up to 384 of the 256 compute units, so that
+// launches may each hold a part of what the others wait for.
 constexpr int BK_THREADS = 1024;
 constexpr int BK_WAVES = BK_THREADS / 64;
 constexpr int BK_PARTS = 8;                     // threads per column
@@ -547,6 +553,7 @@ constexpr int BK_LI = 4 * BK_PARTS;             // local-row stride of a thread'
 constexpr int BK_MAX_P = 64;                    // workgroups per matrix (n <= 16384)
 constexpr int BK_MAX_WG = 96;                   // workgroups per launch
 constexpr unsigned BK_SPIN_LIMIT = 1u << 22;
+constexpr unsigned BK_SPIN_REPAIR = 1u << 15;
 constexpr int BK_TSTR = NB + 4;                 // LDS row stride of T and S (spreads banks)
 constexpr int BK_KMAX = 8;                      // columns per round at most
 // A round stops before pivot j+i (i > 0) when the reflectors j..j+i-1 leave
@@ -613,6 +620,9 @@ struct BlockParams {
   int64_t prev_words;
   int prev_n;
   int P;                     // workgroups per matrix
+  unsigned spin_limit;       // polls of one wait
+  float *bak;                // copy of the block for a repair (or nullptr): column k,
+  int64_t sBak;              // row r of a matrix at k n + r, batch stride sBak
   unsigned *status;          // caller's status word (or nullptr) ...
   unsigned status_bit;       // ... and the bit a give-up or-s into it
 };
@@ -630,9 +640,9 @@ __device__ __forceinline__ unsigned bk_get(const unsigned *p) {
 // reports whether the wait must end (limit reached or abort seen).  Polls
 // back off (s_sleep grows to about 0.2 us) so that waiting workgroups do not
 // crowd out the stores they wait for.
-__device__ __forceinline__ bool bk_give_up(unsigned &spins, unsigned *abort_flag) {
+__device__ __forceinline__ bool bk_give_up(unsigned &spins, unsigned limit, unsigned *abort_flag) {
   ++spins;
-  if (spins >= BK_SPIN_LIMIT) {
+  if (spins >= limit) {
     __hip_atomic_store(abort_flag, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return true;
   }
@@ -658,7 +668,8 @@ constexpr int BK_LOAD_AGENT = 16;   // cache policy operand: sc1
 constexpr int BK_RSRC_WORD3 = 0x00020000;   // buffer resource: raw 32-bit data
 template <int H>
 __device__ __forceinline__ bool bk_gather(__amdgpu_buffer_rsrc_t r, unsigned off, int cnt,
-                                          int xoff, unsigned *abort_flag, float &sum, float &xv) {
+                                          int xoff, unsigned limit, unsigned *abort_flag,
+                                          float &sum, float &xv) {
   static_assert(H <= 32, "one pending bit per item");
   unsigned v[H];
   unsigned pending = cnt >= 32 ? 0xFFFFFFFFu : ((1u << cnt) - 1u);
@@ -685,7 +696,7 @@ __device__ __forceinline__ bool bk_gather(__amdgpu_buffer_rsrc_t r, unsigned off
     }
     pending = still;
     if (pending == 0u && hx) break;
-    if (bk_give_up(spins, abort_flag)) return false;
+    if (bk_give_up(spins, limit, abort_flag)) return false;
   }
   float s = 0.f;
 #pragma unroll
@@ -829,6 +840,16 @@ __global__ __launch_bounds__(BK_THREADS) void qr_block_kernel(BlockParams p) {
         a[i][e] = (col && row < n) ? src[row] : 0.f;
       }
   }
+  if (p.bak && col) {
+    float *keep = p.bak + bz * p.sBak + (unsigned)k * un;
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int row = r0 + BK_LI * i + 4 * part + e;
+        if (row < n) keep[row] = a[i][e];
+      }
+  }
   bool alive = true;
   const bool want_r = p.Rf != nullptr;   // the triangular factor is an output
   // Workgroup 0 keeps a copy of its diagonal rows (local rows < NB) in Ts,
@@ -961,8 +982,8 @@ __global__ __launch_bounds__(BK_THREADS) void qr_block_kernel(BlockParams p) {
             __builtin_amdgcn_make_buffer_rsrc(sl, (short)0, (int)(NB * cw * 4), BK_RSRC_WORD3);
         float ssum = 0.f, xval = 0.f;
         if (alive)
-          alive = bk_gather<H>(rs, (unsigned)(((q * P + g0) * NB + pkq) * 4), cnt, xoff, abort_flag,
-                               ssum, xval);
+          alive = bk_gather<H>(rs, (unsigned)(((q * P + g0) * NB + pkq) * 4), cnt, xoff,
+                               p.spin_limit, abort_flag, ssum, xval);
         float s = ssum;
         if (lg == 1) s = bk_sum2(s);
         else if (lg == 2) s = bk_sum4(s);
@@ -1448,6 +1469,103 @@ __global__ __launch_bounds__(BK_THREADS) void qr_block_kernel(BlockParams p) {
     T[e] = bad ? nan : Ts[(e / NB) * BK_TSTR + e % NB];
 }
 
+// Factors the outer block of each matrix whose exchange was aborted (the
+// failed flag, cleared at the end) from the copy that the block kernel kept:
+// one workgroup per matrix, column by column in memory, with the same
+// reflectors.  A rare case: no launch of it waits, and with nothing failed it
+// ends at once.  S = strict upper part of Y^T Y and T^T are formed in the
+// copy's place (n > 2 NB).
+constexpr int REPAIR_THREADS = 512;
+struct RepairParams {
+  float *At;
+  int64_t sA;
+  int n, c, nb;
+  float *T;
+  int64_t sT;
+  float *dsign, *beta;
+  unsigned *hdr;
+  float *bak;
+  int64_t sBak;
+};
+
+__global__ __launch_bounds__(REPAIR_THREADS) void qr_repair_block_kernel(RepairParams p) {
+  constexpr int WAVES = REPAIR_THREADS / 64;
+  __shared__ float red[WAVES];
+  const int64_t bz = blockIdx.x;
+  unsigned *failed = p.hdr + bz * BK_XHDR + BK_XFAILED;
+  if (__hip_atomic_load(failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u) return;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int n = p.n, nb = p.nb, rows = n - p.c;
+  float *At = p.At + bz * p.sA + (int64_t)p.c * n + p.c;   // column k, row r at k n + r
+  float *bak = p.bak + bz * p.sBak;
+  float *dsign = p.dsign + bz * n + p.c, *betas = p.beta + bz * n + p.c;
+  for (int k = 0; k < nb; ++k)
+    for (int r = t; r < rows; r += REPAIR_THREADS)
+      At[(int64_t)k * n + r] = bak[(int64_t)k * n + p.c + r];
+  __syncthreads();
+  float *S = bak, *Tt = bak + NB * NB;
+  for (int j = 0; j < nb; ++j) {
+    float *x = At + (int64_t)j * n;
+    float st = 0.f;
+    for (int r = j + 1 + t; r < rows; r += REPAIR_THREADS) st += x[r] * x[r];
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) st += __shfl_xor(st, m);
+    if (lane == 0) red[wave] = st;
+    __syncthreads();
+    st = 0.f;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) st += red[w];
+    const float x0 = x[j];
+    float bet = 0.f, inv_v0 = 0.f, rjj = x0;
+    if (st != 0.f) {
+      const float sigma = sqrtf(x0 * x0 + st);
+      const float v0 = (x0 >= 0.f) ? (x0 + sigma) : (x0 - sigma);
+      bet = 2.f * v0 * v0 / (st + v0 * v0);
+      inv_v0 = 1.f / v0;
+      rjj = (x0 >= 0.f) ? -sigma : sigma;
+    }
+    for (int r = j + 1 + t; r < rows; r += REPAIR_THREADS) x[r] *= inv_v0;
+    if (t == 0) {
+      betas[j] = bet;
+      dsign[j] = (rjj < 0.f) ? -1.f : 1.f;
+    }
+    __syncthreads();
+    for (int q = wave; q < nb; q += WAVES) {   // a wave per column
+      if (q == j) continue;
+      float *a = At + (int64_t)q * n;
+      float s = 0.f;
+      for (int r = j + 1 + lane; r < rows; r += 64) s += a[r] * x[r];
+#pragma unroll
+      for (int m = 32; m >= 1; m >>= 1) s += __shfl_xor(s, m);
+      s += a[j];
+      if (q < j) {
+        if (lane == 0) S[q * NB + j] = s;
+      } else {
+        const float f = bet * s;
+        for (int r = j + 1 + lane; r < rows; r += 64) a[r] -= f * x[r];
+        if (lane == 0) a[j] -= f;
+      }
+    }
+    __syncthreads();
+  }
+  for (int k = 0; k < nb; ++k)
+    for (int r = t; r <= k; r += REPAIR_THREADS) At[(int64_t)k * n + r] = (r == k) ? 1.f : 0.f;
+  if (t < nb) {   // row t of T, as column t of T^T
+    for (int j = t; j < nb; ++j) {
+      float s = 0.f;
+      for (int l = t; l < j; ++l) s += Tt[l * NB + t] * S[l * NB + j];
+      Tt[j * NB + t] = (j == t) ? betas[j] : -betas[j] * s;
+    }
+  }
+  __syncthreads();
+  float *T = p.T + bz * p.sT;
+  for (int e = t; e < NB * NB; e += REPAIR_THREADS) {
+    const int k = e / NB, j = e % NB;
+    T[e] = (k <= j && j < nb) ? Tt[j * NB + k] : 0.f;
+  }
+  if (t == 0) __hip_atomic_store(failed, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Final triangular factor: entries of an earlier outer block than their column
 // come from At, except the squares of full pairs (rows of block 2p, columns
 // of block 2p+1, p < np), which the factorization moved to Rf already scaled;
@@ -1726,6 +1844,11 @@ struct QrLayout {
   size_t fv_off;
   int64_t sT, sWbuf, sSk, sPart, sWi;
   int64_t area;        // words of one slot area of the exchange
+  // A batch of several launches per block: failed exchanges are repaired,
+  // from a copy of the block (sBak floats per matrix).
+  bool repair;
+  size_t bak_off;
+  int64_t sBak;
   int64_t sFv;         // the forward Q formation's V = Q Y and V T (n x 2 NB each)
   int64_t sWn, sSkn;   // the near update's own W, W2 (NB x NB each) and split-K partials
   int64_t np;          // pairs of full outer blocks
@@ -1800,6 +1923,10 @@ QrLayout qr_layout(int64_t batch, int64_t n) {
   L.x_off = o;
   L.area = bk_area_words(batch, n);
   if (L.block) o = align256(o + sizeof(unsigned) * (batch * BK_XHDR + 2 * L.area));
+  L.repair = L.block && P0 > 1 && P0 * batch > BK_MAX_WG;
+  L.sBak = (int64_t)NB * n;
+  L.bak_off = o;
+  if (L.repair) o = align256(o + sizeof(float) * batch * L.sBak);
   L.total = o;
   return L;
 }
@@ -1873,6 +2000,7 @@ struct QrCtx {
   float *Tb, *Wb, *W2, *Sk, *Pt, *Wi, *dsign, *betas;
   unsigned *cnt;
   unsigned *xch;
+  float *bak;              // blocks' copies for the repair of failed ones, or nullptr
   // The block launches' use of the two slot areas so far: launches that have
   // exchanged, and what the last of them wrote (as in BlockParams).
   struct Turns {
@@ -1943,7 +2071,10 @@ hipError_t factor_block(const QrCtx &x, int64_t ob, hipStream_t s) {
     BlockParams bp{x.At + b0 * x.sA, x.sA, x.ni, c, nb, x.Tb + b0 * x.L.sT + ob * NB * NB, x.L.sT,
                    x.Rf ? x.Rf + b0 * x.sA : nullptr, x.dsign + b0 * x.n, x.betas + b0 * x.n,
                    hdr, areas + area * x.L.area, pos, area,
-                   t.hdr, areas + (1 - area) * x.L.area, t.words, t.n, P, x.status, x.status_bit};
+                   t.hdr, areas + (1 - area) * x.L.area, t.words, t.n, P,
+                   x.bak ? BK_SPIN_REPAIR : BK_SPIN_LIMIT,
+                   x.bak && P > 1 ? x.bak + b0 * x.L.sBak : nullptr, x.L.sBak,
+                   x.bak ? nullptr : x.status, x.status_bit};
     if (P > 1) {
       if (t.done == 0) {   // area 1 as a whole, if a launch will use it
         bp.prev_words = x.L.area;
@@ -1962,6 +2093,13 @@ hipError_t factor_block(const QrCtx &x, int64_t ob, hipStream_t s) {
       hipLaunchKernelGGL((qr_block_kernel<BK_R, BK_K_MID>), grid, dim3(BK_THREADS), 0, s, bp);
     else
       hipLaunchKernelGGL((qr_block_kernel<BK_R, BK_K_BIG>), grid, dim3(BK_THREADS), 0, s, bp);
+    SOAP_TRY(hipGetLastError());
+  }
+  if (x.bak && P > 1) {
+    const RepairParams rp{x.At, x.sA, x.ni, c, nb, x.Tb + ob * NB * NB, x.L.sT, x.dsign, x.betas,
+                          x.xch, x.bak, x.L.sBak};
+    hipLaunchKernelGGL(qr_repair_block_kernel, dim3((unsigned)x.batch), dim3(REPAIR_THREADS), 0, s,
+                       rp);
     SOAP_TRY(hipGetLastError());
   }
   return hipSuccess;
@@ -2349,6 +2487,8 @@ hipError_t qr_factor_and_form_q(float *At, float *Q, float *Rf, int64_t batch, i
     if (err != hipSuccess) return err;
     const int64_t P0 = (n + BK_ROWS - 1) / BK_ROWS;
     x.L.block = P0 <= std::min(BK_MAX_WG, cap_big);
+    // (several launches per block on a smaller device only with a copy's room)
+    if (P0 > 1 && P0 * batch > cap_big && !x.L.repair) x.L.block = false;
     x.cap_small = std::min(BK_MAX_WG, cap_small);
     x.cap_big = std::min(BK_MAX_WG, cap_big);
   }
@@ -2367,6 +2507,8 @@ hipError_t qr_factor_and_form_q(float *At, float *Q, float *Rf, int64_t batch, i
   x.betas = reinterpret_cast<float *>(base + x.L.b_off);
   x.cnt = reinterpret_cast<unsigned *>(base + x.L.cnt_off);
   x.xch = reinterpret_cast<unsigned *>(base + x.L.x_off);
+  x.bak = x.L.block && x.L.repair ? reinterpret_cast<float *>(base + x.L.bak_off) : nullptr;
+  if (x.bak && Rf) return hipErrorInvalidValue;   // the repair forms no triangular factor
   x.TP = reinterpret_cast<float *>(base + x.L.tp_off);
   x.Sx = reinterpret_cast<float *>(base + x.L.sx_off);
   x.Skp = reinterpret_cast<float *>(base + x.L.skp_off);

@@ -340,3 +340,30 @@ def test_batches_of_several_block_launches(batch, m, n):
         for name in ("Q_L", "Q_R", "V"):
             assert rel(host(getattr(st, name)[b]), host(getattr(one, name))) <= 1e-5, (b, name)
         assert rel(host(W[b]), host(w1)) <= 1e-5, b
+
+
+@pytest.mark.parametrize("batch,m,n", [(50, 513, 300), (49, 257, 770), (20, 1300, 1281)])
+def test_large_batches_never_give_up(batch, m, n):
+    """A batch of several launches per block whose exchanges are all aborted:
+    both sides are factored by the repair, nothing is reported, and both bases
+    are those of the undisturbed step (the same reflectors with the sums in
+    another order: 4 sqrt(d) roundings of the d x d basis)."""
+    import paper_2607_20548_amd as soap
+    G = np.stack([next(iter(_grads(m, n, 1, b))) for b in range(3)])[np.arange(batch) % 3]
+    W0 = 0.02 * np.random.default_rng(2).standard_normal((batch, m, n))
+    out = []
+    for mask in (0, soap.SOAP_STATUS_QR_L | soap.SOAP_STATUS_QR_R):
+        st = soap.SoapState(m, n, batch=batch)
+        W, Gd = dev(W0), dev(G)
+        for t in (1, 2):
+            soap.soap_test_force_qr_give_up(mask)
+            st.step(W, Gd, t, **HP)
+            soap.soap_test_force_qr_give_up(0)
+            assert st.status() == (soap.SOAP_OK, 0)
+        out.append({k: host(getattr(st, k)) for k in ("Q_L", "Q_R")})
+    for name, d in (("Q_L", m), ("Q_R", n)):
+        assert not np.array_equal(out[1][name], out[0][name])
+        for b in (0, batch // 2, batch - 1):
+            e = rel(out[1][name][b], out[0][name][b])
+            log(f"repaired {batch} x {m} x {n} {name}[{b}] {e:.2e}")
+            assert e <= 4 * d ** 0.5 * 2.0 ** -24, (name, b, e)
