@@ -533,9 +533,10 @@ __global__ __launch_bounds__(256) void qr_inner_apply_kernel(ApplyParams p) {
 // Batches of several launches per block (more than BK_MAX_WG workgroups) do
 // not fail: each launch keeps a copy of the block as it was, waits only for
 // BK_SPIN_REPAIR polls (some 50 ms), and qr_repair_block_kernel, which waits
-// for nobody, then factors the blocks of failed matrices again.  Two such
-// steps on two streams ask for up to 384 of the 256 compute units, so that
-// launches may each hold a part of what the others wait for.
+// for nobody, then factors the blocks of failed matrices again.  (The block
+// launches of all of a process's steps follow each other on two streams of a
+// device, so that a launch only lacks room beside another process or kernels
+// that wait themselves.)
 constexpr int BK_THREADS = 1024;
 constexpr int BK_WAVES = BK_THREADS / 64;
 constexpr int BK_PARTS = 8;                     // threads per column
