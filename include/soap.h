@@ -262,6 +262,12 @@ size_t soap_workspace_update_offset(int64_t batch, int64_t m, int64_t n);
  * SOAP_ERR_HPARAM for other bits. */
 int soap_test_force_qr_give_up(uint32_t mask);
 
+/* TEST HOOK, not for production use.  on != 0: every later QR takes the panel
+ * path, which devices (partitions) that cannot hold one matrix's block
+ * workgroups at once take; its kernels wait for nobody.  on = 0 restores the
+ * choice by the device. */
+int soap_test_qr_panel_path(int on);
+
 /* ---- stage entry points (used by the tests to check each kernel alone) ---- */
 
 /* Eigenbasis refresh QR (Algorithm 2, "QR(.).Q"): A = Q Rf for one n x n

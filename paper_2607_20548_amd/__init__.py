@@ -43,6 +43,7 @@ EXPORTED = [
     "soap_kl_factors_workspace_bytes", "soap_kl_factors_f32", "soap_muon_workspace_bytes",
     "soap_muon_step", "soap_muon_step_batched", "soap_workspace_status",
     "soap_workspace_update_offset", "soap_test_force_qr_give_up", "soap_step_noalloc",
+    "soap_test_qr_panel_path",
 ]
 
 
@@ -96,6 +97,7 @@ def lib() -> ctypes.CDLL:
         "soap_workspace_status": (_INT, [_P, ctypes.POINTER(ctypes.c_uint32), _P]),
         "soap_workspace_update_offset": (_SZ, [_I64, _I64, _I64]),
         "soap_test_force_qr_give_up": (_INT, [_U32]),
+        "soap_test_qr_panel_path": (_INT, [_INT]),
         "soap_qr_workspace_bytes": (_SZ, [_I64]),
         "soap_qr_f32": (_INT, [_I64, _P, _P, _P, _P, _SZ, _P]),
         "soap_gemm_f32": (_INT, [_INT, _INT, _I64, _I64, _I64, _F, _P, _I64, _P, _I64, _F, _P,
@@ -176,6 +178,10 @@ def soap_workspace_update_offset(batch: int, m: int, n: int) -> int:
 
 def soap_test_force_qr_give_up(mask: int) -> None:
     _check(lib().soap_test_force_qr_give_up(mask))
+
+
+def soap_test_qr_panel_path(on: bool) -> None:
+    _check(lib().soap_test_qr_panel_path(int(on)))
 
 
 def soap_qr_workspace_bytes(n: int) -> int:

@@ -202,6 +202,7 @@ struct QrSplitOut {
 };
 size_t qr_workspace_bytes(int64_t batch, int64_t n);
 void qr_force_give_up(unsigned mask);
+void qr_force_panel_path(bool on);   // (a test hook)
 // Whether a call over `batch` matrices of order n runs the resident block
 // factorization on the current device with one launch per block.
 hipError_t qr_block_path(int64_t batch, int64_t n, bool *out);

@@ -2415,6 +2415,7 @@ constexpr int FWD_MAX_WG = 160;
 constexpr int64_t FWD_MAX_N = 4096;
 
 std::atomic<unsigned> g_force_give_up{0};
+std::atomic<bool> g_force_panel_path{false};
 
 // Workgroups of one block-kernel launch (R rows per thread) that the current
 // device holds at once, halved: the two factors' QRs of a step may run
@@ -2456,9 +2457,10 @@ int resident_cap(bool small, hipError_t *err) {
 }  // namespace
 
 void qr_force_give_up(unsigned mask) { g_force_give_up.store(mask); }
+void qr_force_panel_path(bool on) { g_force_panel_path.store(on); }
 
 hipError_t qr_block_path(int64_t batch, int64_t n, bool *out) {
-  *out = qr_layout(batch, n).block;
+  *out = qr_layout(batch, n).block && !g_force_panel_path.load();
   if (!*out) return hipSuccess;
   hipError_t err = hipSuccess;
   const int cap_big = resident_cap(false, &err);
@@ -2480,6 +2482,7 @@ hipError_t qr_factor_and_form_q(float *At, float *Q, float *Rf, int64_t batch, i
   if (split && (Rf || batch != 2 * split->half || !split->QA || !split->QB))
     return hipErrorInvalidValue;
   x.cap_small = x.cap_big = BK_MAX_WG;
+  if (g_force_panel_path.load()) x.L.block = false;
   if (x.L.block) {   // resident blocks only where the device holds a matrix's all at once
     hipError_t err = hipSuccess;
     const int cap_big = resident_cap(false, &err);

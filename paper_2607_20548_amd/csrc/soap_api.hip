@@ -1215,6 +1215,11 @@ int soap_test_force_qr_give_up(uint32_t mask) {
   return ok();
 }
 
+int soap_test_qr_panel_path(int on) {
+  soap::qr_force_panel_path(on != 0);
+  return ok();
+}
+
 // Workspace of soap_qr_f32: the status word, A^T, the QR's own buffers.
 size_t soap_qr_workspace_bytes(int64_t n) {
   if (!dim_ok(n)) return 0;

@@ -294,7 +294,17 @@ def test_checkpoint_resume_is_bitwise(kl, batch):
         assert np.array_equal(a[key], b[key]), key
 
 
-def test_batched_step_ignores_what_other_kernels_left_in_lds():
+@pytest.fixture(params=[False, True], ids=["block", "panel"])
+def panel(request):
+    """Both QR paths: the resident blocks, and the panels of devices that cannot
+    hold a matrix's workgroups."""
+    import paper_2607_20548_amd as soap
+    soap.soap_test_qr_panel_path(request.param)
+    yield request.param
+    soap.soap_test_qr_panel_path(False)
+
+
+def test_batched_step_ignores_what_other_kernels_left_in_lds(panel):
     """The step of 64 matrices after products of NaN matrices (whose LDS holds
     NaN on every compute unit) is bit for bit the step before them."""
     import torch

@@ -254,3 +254,55 @@ def test_qr_diagonal_input_gives_exact_identity():
     ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
     soap.soap_qr_f32(n, dev(A), Qd, None, ws, wsb)
     assert np.array_equal(host(Qd), np.eye(n))
+
+
+@pytest.mark.parametrize("n", [1, 3, 130, 257, 700, 1500])
+def test_qr_panel_path_matches_oracle(n):
+    """The panels of devices that cannot hold a matrix's block workgroups."""
+    import paper_2607_20548_amd as soap
+    import oracle
+    import torch
+    A = _well_conditioned(n, 4)
+    Qd = torch.empty((n, n), dtype=torch.float32, device="cuda")
+    Rd = torch.empty((n, n), dtype=torch.float32, device="cuda")
+    wsb = soap.soap_qr_workspace_bytes(n)
+    ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
+    soap.soap_test_qr_panel_path(True)
+    try:
+        soap.soap_qr_f32(n, dev(A), Qd, Rd, ws, wsb)
+    finally:
+        soap.soap_test_qr_panel_path(False)
+    Q, R = host(Qd), host(Rd)
+    A64 = A.astype(np.float64)
+    Qo = oracle.householder_qr(A64)
+    assert column_signs_agree(Q, Qo)
+    assert rel(Q, Qo) <= 1e-4
+    assert np.linalg.norm(Q @ R - A64) / np.linalg.norm(A64) <= 1e-5
+    assert np.linalg.norm(Q.T @ Q - np.eye(n)) / np.sqrt(n) <= 1e-5
+    assert np.all(np.tril(R, -1) == 0) and np.all(np.diag(R) >= 0)
+
+
+@pytest.mark.parametrize("n", [4301, 8450])
+def test_qr_panel_path_equals_the_block_path(n):
+    """Orders whose first panels are 8 and 4 columns wide: the same Q and R as
+    by resident blocks, to the sums' order (4 sqrt(n) roundings, times the
+    condition number of A, below 4)."""
+    import paper_2607_20548_amd as soap
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(n)
+    A = torch.randn(n, n, generator=g, device="cuda") / n ** 0.5 + 4 * torch.eye(n, device="cuda")
+    wsb = soap.soap_qr_workspace_bytes(n)
+    ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
+    out = []
+    for panel in (False, True):
+        Q, R = torch.empty_like(A), torch.empty_like(A)
+        soap.soap_test_qr_panel_path(panel)
+        try:
+            soap.soap_qr_f32(n, A, Q, R, ws, wsb)
+        finally:
+            soap.soap_test_qr_panel_path(False)
+        out.append((Q, R))
+    for a, b in zip(*out):
+        e = float((a.double() - b.double()).norm() / a.double().norm())
+        log(f"panel path n={n} {e:.2e}")
+        assert e <= 16 * n ** 0.5 * 2.0 ** -24
