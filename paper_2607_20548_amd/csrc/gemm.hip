@@ -679,20 +679,18 @@ __global__ __launch_bounds__(256) void splitk_reduce(const float *__restrict__ p
   }
 }
 
-// The same for the lower triangle of a symmetric product: the sum of every
-// element with row >= col goes to (row, col) and (col, row), by 32 x 32 blocks
-// on or below the diagonal (the mirror through LDS).
+// The same without beta for the lower triangle of a symmetric product: the
+// sum of every element with row >= col goes to (row, col) and (col, row), by
+// 32 x 32 blocks on or below the diagonal (the mirror through LDS).
 __global__ __launch_bounds__(256) void splitk_reduce_syrk(const float *__restrict__ part, int S,
                                                           int N, float *C, int64_t ldc, int64_t sC,
-                                                          const float *D, int64_t ldd, int64_t sD,
-                                                          float alpha, float beta) {
+                                                          float alpha) {
   __shared__ float tile[32][33];
   const int bi = blockIdx.y, bj = blockIdx.x;
   if (bj > bi) return;
   const int64_t bz = blockIdx.z, nn = (int64_t)N * N;
   const float *pb = part + bz * S * nn;
   float *Cb = C + bz * sC;
-  const float *Db = D + bz * sD;
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
@@ -701,7 +699,6 @@ __global__ __launch_bounds__(256) void splitk_reduce_syrk(const float *__restric
     if (row < N && col <= row) {
       for (int s = 0; s < S; ++s) v += pb[s * nn + (int64_t)row * N + col];
       v *= alpha;
-      if (beta != 0.f) v += beta * Db[(int64_t)row * ldd + col];
       Cb[(int64_t)row * ldc + col] = v;
     }
     tile[ty + 8 * q][tx] = v;
@@ -776,7 +773,7 @@ hipError_t dispatch(const GemmDesc &d, KParams &kp, hipStream_t s, bool aligned)
   const bool capped = (MODE == MODE_GENERAL || MODE == MODE_SYRK) && d.max_wg > 0 &&
                       (int64_t)kp.ntiles * per_tile > d.max_wg;
   const int code = d.trans_a * 2 + d.trans_b;
-  if (kp.ntiles * per_tile <= SMALL_MAX_TILES && d.max_wg == 0) {
+  if (d.tile == SMALL || (d.tile == 0 && kp.ntiles * per_tile <= SMALL_MAX_TILES && d.max_wg == 0)) {
     set_tiles(kp, SMALL, MODE == MODE_SYRK);
     err = launch_layout<SMALL, MODE, 0, false>(code, aligned, dim3(kp.ntiles, S, (unsigned)d.batch),
                                                s, kp);
@@ -798,7 +795,7 @@ hipError_t dispatch(const GemmDesc &d, KParams &kp, hipStream_t s, bool aligned)
   if (MODE == MODE_SYRK) {
     const unsigned g = (unsigned)((d.N + 31) / 32);
     hipLaunchKernelGGL(splitk_reduce_syrk, dim3(g, g, (unsigned)d.batch), dim3(256), 0, s, kp.part,
-                       S, kp.N, kp.C, kp.ldc, kp.sC, kp.D, kp.ldd, kp.sD, d.alpha, d.beta);
+                       S, kp.N, kp.C, kp.ldc, kp.sC, d.alpha);
     return hipGetLastError();
   }
   int64_t mn = d.M * d.N;
@@ -863,20 +860,21 @@ int choose_splitk(int64_t M, int64_t N, int64_t K, int64_t batch, int max_split)
   return (int)s;
 }
 
-// A triangle of at most 256 64-tiles is split into about two workgroups per CU
-// of at least 256 of K each (517^2, K = 1283, 45 tiles: 80 -> 27 + 8 us); one of
-// more, but of few 128-tiles (whose compute units would hold one tile or
+// A triangle of at most 256 64-tiles (over the batch) is split, as 64-tiles,
+// into about two workgroups per CU of at least 256 of K each (517^2, K = 1283,
+// 45 tiles: 80 -> 27 + 8 us); one of more, but of few 128-tiles (whose compute units would hold one tile or
 // none), into 128-tiles of at least 1024 of K each where two slices or more
 // fit two workgroups per CU (2048^2, K = 8192, 136 of them: the Muon step of
 // 2048 x 8192 13.0 -> 11.6 ms).
-int choose_syrk_split(int64_t d, int64_t K, int64_t batch) {
+SyrkSplit choose_syrk_split(int64_t d, int64_t K, int64_t batch) {
   const int64_t t1 = (d + SMALL - 1) / SMALL, n1 = t1 * (t1 + 1) / 2 * batch;
   const int64_t t2 = (d + BIG - 1) / BIG, n2 = t2 * (t2 + 1) / 2 * batch;
-  if (n1 <= 0) return 1;
+  if (n1 <= 0) return {1, 0};
   int64_t s = 1;
   if (n1 <= 256) s = std::min<int64_t>({8, 512 / n1, K / 256});
   else if (n2 * 2 > SMALL_MAX_TILES) s = std::min<int64_t>({8, 512 / n2, K / 1024});
-  return (int)std::max<int64_t>(1, s);
+  if (s <= 1) return {1, 0};
+  return {(int)s, n1 <= 256 ? SMALL : BIG};
 }
 
 hipError_t launch_gemm(const GemmDesc &d, hipStream_t s) {
@@ -888,6 +886,7 @@ hipError_t launch_gemm(const GemmDesc &d, hipStream_t s) {
 
 hipError_t launch_syrk_ema(const GemmDesc &d, hipStream_t s) {
   if (d.M <= 0 || d.batch <= 0) return hipSuccess;
+  if (d.splitk > 1 && (d.D || d.beta != 0.f)) return hipErrorInvalidValue;
   KParams kp = make_params(d, true);
   return dispatch<MODE_SYRK>(d, kp, s, aligned_loads(d));
 }

@@ -27,7 +27,7 @@ struct GemmDesc {
   int64_t ldc = 0, sC = 0;
   float alpha = 1.f, beta = 0.f;
   // If set, beta applies to D instead of C: C = alpha op(A) op(B) + beta D (not
-  // with split-K of a general product, nor in the Adam form).
+  // with split-K, nor in the Adam form).
   const float *D = nullptr;
   int64_t ldd = 0, sD = 0;
   int64_t batch = 1;
@@ -46,6 +46,8 @@ struct GemmDesc {
   // are launched and each loops over tiles: the product then holds only part
   // of the compute units, leaving the rest to concurrent work.
   int max_wg = 0;
+  // Tile rows and columns, 64 or 128 (0: by the number of tiles).
+  int tile = 0;
   // If set, the product of batch entry b is not computed (C, and the split-K
   // partials, are left untouched) when skip[b * sSkip] != 0 at launch time.
   const unsigned *skip = nullptr;
@@ -57,8 +59,11 @@ struct GemmDesc {
 int choose_splitk(int64_t M, int64_t N, int64_t K, int64_t batch, int max_split);
 
 // A split-K factor for launch_syrk_ema on a d x d triangle with few tiles and
-// long K (1: not split): about two 64-tiles per CU, at least 256 of K each.
-int choose_syrk_split(int64_t d, int64_t K, int64_t batch);
+// long K (1: not split), and the tile of the slices.
+struct SyrkSplit {
+  int split, tile;
+};
+SyrkSplit choose_syrk_split(int64_t d, int64_t K, int64_t batch);
 
 // C = alpha op(A) op(B) + beta C (C not read when beta == 0).
 hipError_t launch_gemm(const GemmDesc &d, hipStream_t s);
@@ -68,7 +73,8 @@ hipError_t launch_gemm(const GemmDesc &d, hipStream_t s);
 // diagonal scaling folded into B), only tiles on or below the diagonal are
 // computed and each result is stored at (i,j) and (j,i).  C is read from its
 // lower triangle (or D, if set, from its).  max_wg caps it like a GEMM for the
-// layouts (0, 1) and (1, 0).  With split-K the partials hold the lower tiles.
+// layouts (0, 1) and (1, 0).  With split-K the partials hold the lower tiles
+// and beta must be 0.
 hipError_t launch_syrk_ema(const GemmDesc &d, hipStream_t s);
 
 // Fused second rotation + Adam in the eigenbasis.  op(A) (trans_a = 0,

@@ -805,7 +805,7 @@ int step_impl(int64_t batch, float *param, const float *grad, float *L, float *R
 // ------------------------------------------------------------------ Muon
 struct MuonLayout {
   size_t x, xn, a, bm, part, inv, sk, total;
-  int split;   // K slices of the fp32 Gram product (sk: their partials)
+  soap::SyrkSplit split;   // K slices of the fp32 Gram product (sk: their partials)
 };
 
 MuonLayout muon_layout(int64_t batch, int64_t m, int64_t n) {
@@ -820,7 +820,7 @@ MuonLayout muon_layout(int64_t batch, int64_t m, int64_t n) {
   L.part = o; o = align256(o + soap::muon_norm_partial_bytes(batch));
   L.inv = o; o = align256(o + f * batch);
   L.split = soap::choose_syrk_split(d, std::max(m, n), batch);
-  L.sk = o; o = align256(o + (L.split > 1 ? f * batch * L.split * d * d : 0));
+  L.sk = o; o = align256(o + (L.split.split > 1 ? f * batch * L.split.split * d * d : 0));
   L.total = o;
   return L;
 }
@@ -974,7 +974,8 @@ int muon_impl(int64_t batch, float *param, const float *grad, float *M, int64_t 
       g.M = d; g.N = d; g.K = e2;
       g.A = X; g.lda = n; g.sA = mn; g.B = X; g.ldb = n; g.sB = mn;
       g.C = A; g.ldc = d; g.sC = dd; g.alpha = 1.f; g.beta = 0.f; g.batch = batch;
-      g.splitk = lay.split;
+      g.splitk = lay.split.split;
+      g.tile = lay.split.tile;
       g.part = reinterpret_cast<float *>(w + lay.sk);
       if ((e = soap::launch_syrk_ema(g, s)) != hipSuccess) return hip_fail(e, "Newton-Schulz A");
     }

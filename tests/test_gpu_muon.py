@@ -125,11 +125,13 @@ def test_muon_bench_shape():
 
 
 @pytest.mark.parametrize("batch,m,n", [(1, 130, 1030), (1, 2051, 65), (3, 100, 515), (1, 520, 520),
-                                       (2, 1100, 1000)])
+                                       (2, 1100, 1000), (128, 64, 1024), (40, 1100, 33),
+                                       (1, 1701, 4099)])
 def test_gram_products_split_over_k(batch, m, n):
     """Wide and tall weights whose Gram product is split over K (edges of the
-    64-tiles and of the slices), square ones whose is not: one step against the
-    fp64 iteration."""
+    64-tiles and of the slices, a square one of two slices, batches of one
+    64-tile each, 128-tiles in slices of odd K), and one of too many tiles for
+    it (2 x 1100 x 1000): one step against the fp64 iteration."""
     import torch
     import paper_2607_20548_amd as soap
     g = torch.Generator(device="cuda").manual_seed(m)
