@@ -261,7 +261,9 @@ __device__ __forceinline__ void tile_coords(const KParams &p, int t, int &tm, in
 // Two workgroups per CU (256 registers per lane: accumulators, one or two
 // blocks' slab sums, the slab in flight and the fragments of a block), whose
 // loads, splits and matrix instructions overlap one another; bounded to
-// three, the slab sums spill (180 -> 89 TFLOP/s).
+// three, the slab sums spill (180 -> 89 TFLOP/s).  Most V_ANY forms (odd sizes)
+// keep 8 to 36 bytes per lane in scratch even so: a few words moved per slab,
+// none among its matrix instructions.
 //
 // BT = 64 is for products with few tiles (four waves of one 32 x 32 block
 // each): four times the workgroups, a quarter of the work in each, and three
@@ -750,11 +752,11 @@ hipError_t launch_layout(int code, bool aligned, dim3 grid, hipStream_t s, const
 
 // Products of at most this many 128-tiles (split slices and batch included)
 // take 64-tiles: below it compute units stay idle with 128-tiles and each
-// tile's chain of slabs is what takes the time (128 x 128 x 128: 17 -> 8 us;
-// 517 x 517 x 1283, 25 tiles: 132 -> 49; 1536^3, 144 tiles: 112 -> 83; a
-// triangle of 136 tiles, K = 2048: 141 -> 92); from 256 tiles on the larger
-// tile's fewer bytes per flop win (2048^3: 151 us with 128-tiles, 163 with
-// 64-tiles; 3072 x 2048 x 2048, 384 tiles: 173 and 209).
+// tile's chain of slabs is what takes the time (128 x 128 x 128: 16 -> 9 us;
+// 517 x 517 x 1283, 25 tiles: 162 -> 66; 1536^3, 144 tiles: 114 -> 85; a
+// triangle of 136 tiles, K = 2048: 138 -> 100); from 256 tiles on the larger
+// tile's fewer bytes per flop win (2048^3: 155 us with 128-tiles, 172 with
+// 64-tiles; 3072 x 2048 x 2048, 384 tiles: 187 and 231).
 constexpr int64_t SMALL_MAX_TILES = 192;
 
 void set_tiles(KParams &kp, int bt, bool triangle) {

@@ -491,13 +491,13 @@ __global__ __launch_bounds__(256) void axpby_bf16_kernel(float *__restrict__ W,
 
 }  // namespace
 
-// 256-tiles from half the compute units' count of them on (figures of eight
-// waves per tile): the iterations of 4096 x 4096 (triangles of 136 tiles, 256
-// in the third product) take 6.94 ms with them throughout and 7.77 when the
-// triangles keep 128-tiles; 2048 x 8192 (triangles of 36 tiles) 6.84 ms with
-// and 4.62 without.  64-tiles while
-// 128-tiles would leave compute units idle: 1024 x 1024 1.64 -> 0.96 ms, 1536
-// x 3072 2.44 -> 1.95; a bound of 400 instead of 192 within 2% either way.
+// 256-tiles from half the compute units' count of them on, 16 iterations of
+// each: triangles of 136 tiles (4096 x 4096) take 5.65 ms in them and 7.11 in
+// 128-tiles, of 105 (3584 x 3584) 4.74 and 4.30; full products of 144
+// (3072 x 3072) 3.63 and 4.43, of 120 and 128 the same, of 100 (2560 x 2560)
+// 2.78 and 2.62, of 72 (1536 x 3072) 1.85 and 1.76.  64-tiles while 128-tiles
+// would leave compute units idle: 1024 x 1024 1.38 -> 0.79 ms, 1536 x 3072 2.21
+// -> 1.75; the same with a bound of 400 instead of 192.
 static constexpr int64_t MIN_TILES_256 = 128;
 static constexpr int64_t MAX_TILES_64 = 192;
 
