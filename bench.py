@@ -24,8 +24,9 @@ matrices of four shapes; one soap_step per matrix from one host loop, or with
 --group one soap_step_batched per shape).  These reuse one gradient per
 matrix for every step.
 
-Prints ONE JSON line.  `value` is steps/s of the whole step; `roofline`
-describes the dominant kernel (timed with HIP events on the library's stream
+Prints ONE JSON line.  `value` is steps/s of the whole step; fractions of
+the matrix peak are of a sixth of the bfloat16 peak for fp32 products, each of
+which is six bfloat16 ones; `roofline` describes the dominant kernel (timed with HIP events on the library's stream
 through the soap_timing_* API); `cpu_baseline` times the fp64 oracle on a
 bounded sample of the same workload.
 """
@@ -41,7 +42,6 @@ import numpy as np
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
-PEAK_FP32_MFMA_TFLOPS = 157.3   # MI355X dense fp32 matrix peak (256 CU x 256 flop/clk x 2.4 GHz)
 PEAK_BF16_MFMA_TFLOPS = 2500.0  # MI355X dense bf16 matrix peak (datasheet, no sparsity)
 PEAK_SPLIT_TFLOPS = PEAK_BF16_MFMA_TFLOPS / 6   # fp32 products as six bf16 partial products
 PEAK_HBM_GBS = 8000.0
@@ -126,7 +126,7 @@ def bench_muon(args, soap, torch, sg):
                    "m": m, "n": n, "rank": spec.rank, "global_batch": 1, "seq_len": None,
                    "parallelism": "none (1 GPU)"},
         "step_tflops": F * value / 1e12,
-        "step_frac_of_fp32_mfma_peak": F * value / 1e12 / PEAK_FP32_MFMA_TFLOPS,
+        "step_frac_of_mfma_peak": F * value / 1e12 / peak,
         "roofline": {"bound": "mfma", "kernel": "muon_newton_schulz (SYRK + two GEMMs per "
                                                 "iteration)",
                      "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
@@ -215,7 +215,7 @@ def bench_workload(args, soap, torch, sg):
         "config": {"workload": desc[args.workload], "matrices": len(specs),
                    "shapes": sorted(groups.keys()), "parallelism": "none (1 GPU)"},
         "step_tflops": total_flops * value / 1e12,
-        "step_frac_of_fp32_mfma_peak": total_flops * value / 1e12 / PEAK_FP32_MFMA_TFLOPS,
+        "step_frac_of_mfma_peak": total_flops * value / 1e12 / PEAK_SPLIT_TFLOPS,
     }
     print(json.dumps(out), flush=True)
 
@@ -401,7 +401,7 @@ def main():
                    "m": m, "n": n, "rank": spec.rank, "global_batch": 1, "seq_len": None,
                    "parallelism": "none (1 GPU)"},
         "step_tflops": F * value / 1e12,
-        "step_frac_of_fp32_mfma_peak": F * value / 1e12 / PEAK_FP32_MFMA_TFLOPS,
+        "step_frac_of_mfma_peak": F * value / 1e12 / PEAK_SPLIT_TFLOPS,
         "roofline": roofline,
         "stage_ms_per_step": {k: v[0] / nst for k, v in stages.items() if v[1] > 0},
     }
@@ -413,8 +413,8 @@ def main():
     if q_n and q_ms > 0:
         out["qr"] = {"stage": qr_name, "n": max(m, n), "ms": q_ms / q_n,
                      "tflops": q_fl / q_n / (q_ms / q_n * 1e-3) / 1e12,
-                     "frac_of_fp32_mfma_peak": q_fl / q_n / (q_ms / q_n * 1e-3) / 1e12
-                     / PEAK_FP32_MFMA_TFLOPS,
+                     "frac_of_mfma_peak": q_fl / q_n / (q_ms / q_n * 1e-3) / 1e12
+                     / PEAK_SPLIT_TFLOPS,
                      "share_of_step": (q_ms / nst) / (1e3 * elapsed / args.steps),
                      "flops": "(8/3) n^3 per factor: Householder factorization and explicit Q"}
     if not args.no_cpu_baseline:

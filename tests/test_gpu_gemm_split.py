@@ -135,8 +135,10 @@ def test_infinite_and_huge_operands(soap):
 
 
 def test_long_sums_of_one_sign(soap):
-    """K = 6144 products of one sign: below half of what a plain fp32
-    accumulation in order may lose, K / 2 x 2^-24."""
+    """K = 6144 products of one sign: each slab's sum is rounded into the
+    accumulator once, so that the error stays below an eighth of the bound
+    (K / 32 + 12) 2^-24 (a sixtieth of the K / 2 x 2^-24 that accumulating in
+    order may lose)."""
     import torch
     K = 6144
     A = torch.rand(128, K, device="cuda") + 0.5
