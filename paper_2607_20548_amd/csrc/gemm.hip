@@ -15,12 +15,11 @@
 // and 1.6e-6 on v_mfma_f32_32x32x2_f32.  Operands are split once, on the way
 // to LDS, scaled so that bfloat16's range holds their parts (see SCALE); sums
 // that overflow are handled after the K loop (see there).
-// Measured: 4096^3 1150 -> 870 us and 14336^3 (both operands x-contiguous)
-// 44.0 -> 37.7 ms against the fp32 instructions, i.e. 156-179 TFLOP/s
-// of products, 0.95-1.1 PFLOP/s of bfloat16 matrix work; the same launches on
+// Measured: 4096^3 1150 -> 855 us and 14336^3 (both operands x-contiguous)
+// 44.0 -> 34.5 ms against the fp32 instructions, i.e. 161-187 TFLOP/s
+// of products, 1.0-1.1 PFLOP/s of bfloat16 matrix work; the same launches on
 // zero operands ran at 205-234, so that the card's power bounds the large
-// products (a large library product in bfloat16 runs at 1.37 PFLOP/s).  The
-// scaling is one multiplication per loaded value (850 and 35.6 without).
+// products (a large library product in bfloat16 runs at 1.37 PFLOP/s).
 //
 // Tiling: a 256-thread workgroup (4 wave64s in a 2 x 2 arrangement) computes a
 // 128 x 128 tile of C (64 x 64 for products with few tiles); each wave owns a
@@ -73,7 +72,8 @@ struct Lds {
 // smallest fp32 value, 2^-149, becomes 2^-133, the smallest bfloat16, so that
 // the three parts hold every operand exactly (the matrix instructions keep
 // bfloat16's subnormals).  Unscaled, operands below 2^-110 lost bits: 1e-37
-// times 1e12 came out with a relative error of 3e-4.
+// times 1e12 came out with a relative error of 3e-4.  It takes one
+// multiplication per loaded value, 1 to 2% of a product.
 constexpr float SCALE = 65536.f;
 constexpr float UNSCALE = 1.f / (SCALE * SCALE);
 
@@ -105,7 +105,16 @@ struct KParams {
 };
 
 struct f4u { float x, y, z, w; };   // 4-byte aligned
-struct f2u { float x, y; };
+typedef v2f v2fu __attribute__((aligned(4)));
+
+// A wave-uniform address kept in scalar registers, for loads at a 32-bit
+// offset from it.
+typedef const __attribute__((address_space(1))) char *GlobalBytes;
+__device__ __forceinline__ GlobalBytes uniform_row(const float *p) {
+  uint64_t a = reinterpret_cast<uint64_t>(p);
+  asm("" : "+s"(a));
+  return reinterpret_cast<GlobalBytes>(a);
+}
 
 // Two floats as three bfloat16 pairs with SCALE x = hi + mid + lo exactly
 // (for |x| below 2^111, past which a part is infinite): each part is the
@@ -181,22 +190,28 @@ struct SlabLoader {
       }
     } else {
       // k is uniform within a wave: the row address is formed on the scalar
-      // unit and each lane adds its column offset.
+      // unit.  In 128-tiles, whose vector unit is as busy as the matrix
+      // cores, the rows' addresses follow each other there and stay there,
+      // with the lane's offset as the load's own 32-bit one (a 64-bit
+      // addition per load otherwise: 14336^3 37.0 -> 34.5 ms); the short
+      // chains of 64-tiles are slower with it (517 x 517 x 1283 66 -> 69 us).
       const int k = k0 + 8 * __builtin_amdgcn_readfirstlane(tid >> 6);
       if (RPT == 2 && (LOADS == V_ALIGNED || X > 1)) {
-        const int x = x0 + 2 * (tid & 63);
-        const unsigned xc = (unsigned)min(x, X - 2);
+        const int x = x0 + 2 * (tid & 63), xb = min(x0, X - 2);
+        unsigned xc = 4u * (unsigned)(min(x, X - 2) - xb);
+        asm volatile("" : "+v"(xc));   // widened at its loads, as their offset field
         // an odd X: the last row is the second of the clamped pair
         const bool odd = LOADS == V_ANY && x == X - 1;
+        const float *row = base + (int64_t)min(k, K - 1) * ld + xb;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float *rowp = base + (int64_t)min(k + e, K - 1) * ld;
+        for (int e = 0; e < 8; ++e, row += k + e < K ? ld : 0) {
+          const GlobalBytes rowp = uniform_row(row);
           float vx, vy;
           if (LOADS == V_ALIGNED) {
-            const float2 v = *reinterpret_cast<const float2 *>(rowp + xc);
+            const v2f v = *reinterpret_cast<const __attribute__((address_space(1))) v2f *>(rowp + xc);
             vx = v.x; vy = v.y;
           } else {
-            const f2u v = *reinterpret_cast<const f2u *>(rowp + xc);
+            const v2fu v = *reinterpret_cast<const __attribute__((address_space(1))) v2fu *>(rowp + xc);
             vx = v.x; vy = v.y;
           }
           r[0][e] = odd ? vy : vx;
