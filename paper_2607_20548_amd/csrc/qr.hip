@@ -621,9 +621,8 @@ struct BlockParams {
   int64_t prev_words;
   int prev_n;
   int P;                     // workgroups per matrix
-  unsigned spin_limit;       // polls of one wait
-  float *bak;                // copy of the block for a repair (or nullptr): column k,
-  int64_t sBak;              // row r of a matrix at k n + r, batch stride sBak
+  float *bak;                // REPAIR: copy of the block, column k, row r of a matrix
+  int64_t sBak;              // at k n + r, batch stride sBak
   unsigned *status;          // caller's status word (or nullptr) ...
   unsigned status_bit;       // ... and the bit a give-up or-s into it
 };
@@ -641,9 +640,10 @@ __device__ __forceinline__ unsigned bk_get(const unsigned *p) {
 // reports whether the wait must end (limit reached or abort seen).  Polls
 // back off (s_sleep grows to about 0.2 us) so that waiting workgroups do not
 // crowd out the stores they wait for.
-__device__ __forceinline__ bool bk_give_up(unsigned &spins, unsigned limit, unsigned *abort_flag) {
+template <unsigned LIMIT>
+__device__ __forceinline__ bool bk_give_up(unsigned &spins, unsigned *abort_flag) {
   ++spins;
-  if (spins >= limit) {
+  if (spins >= LIMIT) {
     __hip_atomic_store(abort_flag, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return true;
   }
@@ -667,10 +667,9 @@ __device__ __forceinline__ bool bk_give_up(unsigned &spins, unsigned limit, unsi
 // there are.  false: aborted.
 constexpr int BK_LOAD_AGENT = 16;   // cache policy operand: sc1
 constexpr int BK_RSRC_WORD3 = 0x00020000;   // buffer resource: raw 32-bit data
-template <int H>
+template <int H, unsigned LIMIT>
 __device__ __forceinline__ bool bk_gather(__amdgpu_buffer_rsrc_t r, unsigned off, int cnt,
-                                          int xoff, unsigned limit, unsigned *abort_flag,
-                                          float &sum, float &xv) {
+                                          int xoff, unsigned *abort_flag, float &sum, float &xv) {
   static_assert(H <= 32, "one pending bit per item");
   unsigned v[H];
   unsigned pending = cnt >= 32 ? 0xFFFFFFFFu : ((1u << cnt) - 1u);
@@ -697,7 +696,7 @@ __device__ __forceinline__ bool bk_gather(__amdgpu_buffer_rsrc_t r, unsigned off
     }
     pending = still;
     if (pending == 0u && hx) break;
-    if (bk_give_up(spins, limit, abort_flag)) return false;
+    if (bk_give_up<LIMIT>(spins, abort_flag)) return false;
   }
   float s = 0.f;
 #pragma unroll
@@ -771,7 +770,10 @@ constexpr int BK_K_SMALL = 8;
 // R diagonal, (unused), gamma_i[l], c_i[l], p_l[i] (l < K).
 constexpr int bk_prm_words(int K) { return 4 + 3 * K; }
 
-template <int R, int KM>
+// REPAIR: a launch whose failed matrices are factored again (a form of its
+// own: with the limit and the copy as run-time choices every launch took 3 us
+// longer).
+template <int R, int KM, bool REPAIR = false>
 __global__ __launch_bounds__(BK_THREADS) void qr_block_kernel(BlockParams p) {
   static_assert(KM >= 1 && KM <= BK_KMAX, "columns per round");
   constexpr int NI = R / 4;
@@ -841,7 +843,7 @@ __global__ __launch_bounds__(BK_THREADS) void qr_block_kernel(BlockParams p) {
         a[i][e] = (col && row < n) ? src[row] : 0.f;
       }
   }
-  if (p.bak && col) {
+  if (REPAIR && col) {
     float *keep = p.bak + bz * p.sBak + (unsigned)k * un;
 #pragma unroll
     for (int i = 0; i < NI; ++i)
@@ -983,8 +985,8 @@ __global__ __launch_bounds__(BK_THREADS) void qr_block_kernel(BlockParams p) {
             __builtin_amdgcn_make_buffer_rsrc(sl, (short)0, (int)(NB * cw * 4), BK_RSRC_WORD3);
         float ssum = 0.f, xval = 0.f;
         if (alive)
-          alive = bk_gather<H>(rs, (unsigned)(((q * P + g0) * NB + pkq) * 4), cnt, xoff,
-                               p.spin_limit, abort_flag, ssum, xval);
+          alive = bk_gather<H, REPAIR ? BK_SPIN_REPAIR : BK_SPIN_LIMIT>(
+              rs, (unsigned)(((q * P + g0) * NB + pkq) * 4), cnt, xoff, abort_flag, ssum, xval);
         float s = ssum;
         if (lg == 1) s = bk_sum2(s);
         else if (lg == 2) s = bk_sum4(s);
@@ -2048,6 +2050,17 @@ BlockPlan block_plan(const QrCtx &x, int64_t ob) {
   return b;
 }
 
+template <bool REPAIR>
+void launch_block(bool small, int P, dim3 grid, hipStream_t s, const BlockParams &bp) {
+  const dim3 threads(BK_THREADS);
+  if (small)
+    hipLaunchKernelGGL((qr_block_kernel<BK_R_SMALL, BK_K_SMALL, REPAIR>), grid, threads, 0, s, bp);
+  else if (P <= BK_MID_MAX_P)
+    hipLaunchKernelGGL((qr_block_kernel<BK_R, BK_K_MID, REPAIR>), grid, threads, 0, s, bp);
+  else
+    hipLaunchKernelGGL((qr_block_kernel<BK_R, BK_K_BIG, REPAIR>), grid, threads, 0, s, bp);
+}
+
 // Factors outer block ob on stream s (resident-block kernel or panel path).
 // A batch whose workgroups cannot all be resident takes several launches in
 // turn, each over as many matrices as can be (any number when a matrix is
@@ -2073,8 +2086,7 @@ hipError_t factor_block(const QrCtx &x, int64_t ob, hipStream_t s) {
                    x.Rf ? x.Rf + b0 * x.sA : nullptr, x.dsign + b0 * x.n, x.betas + b0 * x.n,
                    hdr, areas + area * x.L.area, pos, area,
                    t.hdr, areas + (1 - area) * x.L.area, t.words, t.n, P,
-                   x.bak ? BK_SPIN_REPAIR : BK_SPIN_LIMIT,
-                   x.bak && P > 1 ? x.bak + b0 * x.L.sBak : nullptr, x.L.sBak,
+                   x.bak ? x.bak + b0 * x.L.sBak : nullptr, x.L.sBak,
                    x.bak ? nullptr : x.status, x.status_bit};
     if (P > 1) {
       if (t.done == 0) {   // area 1 as a whole, if a launch will use it
@@ -2087,13 +2099,8 @@ hipError_t factor_block(const QrCtx &x, int64_t ob, hipStream_t s) {
       t.n = cnt;
     }
     const dim3 grid((unsigned)P, (unsigned)cnt);
-    if (b.small)
-      hipLaunchKernelGGL((qr_block_kernel<BK_R_SMALL, BK_K_SMALL>), grid, dim3(BK_THREADS), 0, s,
-                         bp);
-    else if (P <= BK_MID_MAX_P)
-      hipLaunchKernelGGL((qr_block_kernel<BK_R, BK_K_MID>), grid, dim3(BK_THREADS), 0, s, bp);
-    else
-      hipLaunchKernelGGL((qr_block_kernel<BK_R, BK_K_BIG>), grid, dim3(BK_THREADS), 0, s, bp);
+    if (x.bak && P > 1) launch_block<true>(b.small, P, grid, s, bp);
+    else launch_block<false>(b.small, P, grid, s, bp);
     SOAP_TRY(hipGetLastError());
   }
   if (x.bak && P > 1) {
