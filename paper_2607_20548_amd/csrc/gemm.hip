@@ -191,10 +191,12 @@ struct SlabLoader {
     } else {
       // k is uniform within a wave: the row address is formed on the scalar
       // unit.  In 128-tiles, whose vector unit is as busy as the matrix
-      // cores, the rows' addresses follow each other there and stay there,
-      // with the lane's offset as the load's own 32-bit one (a 64-bit
-      // addition per load otherwise: 14336^3 37.0 -> 34.5 ms); the short
-      // chains of 64-tiles are slower with it (517 x 517 x 1283 66 -> 69 us).
+      // cores, it stays there, with the lane's offset as the load's own
+      // 32-bit one (a 64-bit addition per load otherwise: 14336^3 37.0 ->
+      // 34.4 ms), and the rows of a whole slab follow each other by additions
+      // (a clamp and a 64-bit product per row otherwise: 4096^3 793 -> 774 us).
+      // The short chains of 64-tiles were slower with it (517 x 517 x 1283 66
+      // -> 69 us).
       const int k = k0 + 8 * __builtin_amdgcn_readfirstlane(tid >> 6);
       if (RPT == 2 && (LOADS == V_ALIGNED || X > 1)) {
         const int x = x0 + 2 * (tid & 63), xb = min(x0, X - 2);
@@ -202,9 +204,7 @@ struct SlabLoader {
         asm volatile("" : "+v"(xc));   // widened at its loads, as their offset field
         // an odd X: the last row is the second of the clamped pair
         const bool odd = LOADS == V_ANY && x == X - 1;
-        const float *row = base + (int64_t)min(k, K - 1) * ld + xb;
-#pragma unroll
-        for (int e = 0; e < 8; ++e, row += k + e < K ? ld : 0) {
+        auto get = [&](int e, const float *row) {
           const GlobalBytes rowp = uniform_row(row);
           float vx, vy;
           if (LOADS == V_ALIGNED) {
@@ -216,6 +216,14 @@ struct SlabLoader {
           }
           r[0][e] = odd ? vy : vx;
           r[RPT - 1][e] = vy;
+        };
+        if (k0 + BK <= K) {
+          const float *row = base + (int64_t)k * ld + xb;
+#pragma unroll
+          for (int e = 0; e < 8; ++e, row += ld) get(e, row);
+        } else {   // the ragged slab (or past the end)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) get(e, base + (int64_t)min(k + e, K - 1) * ld + xb);
         }
       } else {   // one row per thread (or a single row in all)
         const unsigned xc = (unsigned)min(x0 + (tid & 63), X - 1);
