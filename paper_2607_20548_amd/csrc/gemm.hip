@@ -285,7 +285,7 @@ __device__ __forceinline__ void tile_coords(const KParams &p, int t, int &tm, in
 // blocks' slab sums, the slab in flight and the fragments of a block), whose
 // loads, splits and matrix instructions overlap one another; bounded to
 // three, the slab sums spill (180 -> 89 TFLOP/s).  Most V_ANY forms (odd sizes)
-// keep 8 to 36 bytes per lane in scratch even so: a few words moved per slab,
+// keep 8 to 20 bytes per lane in scratch even so: a few words moved per slab,
 // none among its matrix instructions.
 //
 // BT = 64 is for products with few tiles (four waves of one 32 x 32 block
