@@ -26,9 +26,9 @@ matrix for every step.
 
 Prints ONE JSON line.  `value` is steps/s of the whole step; fractions of
 the matrix peak are of a sixth of the bfloat16 peak for fp32 products, each of
-which is six bfloat16 ones; `roofline` describes the dominant kernel (timed with HIP events on the library's stream
-through the soap_timing_* API); `cpu_baseline` times the fp64 oracle on a
-bounded sample of the same workload.
+which is six bfloat16 ones; `roofline` describes the dominant kernel (timed
+with HIP events on the library's stream through the soap_timing_* API);
+`cpu_baseline` times the fp64 oracle on a bounded sample of the same workload.
 """
 import argparse
 import hashlib

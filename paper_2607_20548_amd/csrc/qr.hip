@@ -532,7 +532,7 @@ __global__ __launch_bounds__(256) void qr_inner_apply_kernel(ApplyParams p) {
 // into its status word.
 // Batches of several launches per block (more than BK_MAX_WG workgroups) do
 // not fail: each launch keeps a copy of the block as it was, waits only for
-// BK_SPIN_REPAIR polls (some 50 ms), and qr_repair_block_kernel, which waits
+// BK_SPIN_REPAIR polls (tens of milliseconds), and qr_repair_block_kernel, which waits
 // for nobody, then factors the blocks of failed matrices again.  (The block
 // launches of all of a process's steps follow each other on two streams of a
 // device, so that a launch only lacks room beside another process or kernels
