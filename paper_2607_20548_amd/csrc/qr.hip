@@ -532,11 +532,11 @@ __global__ __launch_bounds__(256) void qr_inner_apply_kernel(ApplyParams p) {
 // into its status word.
 // Batches of several launches per block (more than BK_MAX_WG workgroups) do
 // not fail: each launch keeps a copy of the block as it was, waits only for
-// BK_SPIN_REPAIR polls (tens of milliseconds), and qr_repair_block_kernel, which waits
-// for nobody, then factors the blocks of failed matrices again.  (The block
-// launches of all of a process's steps follow each other on two streams of a
-// device, so that a launch only lacks room beside another process or kernels
-// that wait themselves.)
+// BK_SPIN_REPAIR polls (tens of milliseconds), and qr_repair_block_kernel,
+// which waits for nobody, then factors the blocks of failed matrices again.
+// (The block launches of all of a process's steps follow each other on two
+// streams of a device, so that a launch only lacks room beside another process
+// or kernels that wait themselves.)
 constexpr int BK_THREADS = 1024;
 constexpr int BK_WAVES = BK_THREADS / 64;
 constexpr int BK_PARTS = 8;                     // threads per column
@@ -2089,6 +2089,7 @@ hipError_t factor_block(const QrCtx &x, int64_t ob, hipStream_t s) {
                    x.bak ? x.bak + b0 * x.L.sBak : nullptr, x.L.sBak,
                    x.bak ? nullptr : x.status, x.status_bit};
     if (P > 1) {
+      if (cnt * pos > x.L.area) return hipErrorInvalidValue;   // (cannot be: see bk_area_words)
       if (t.done == 0) {   // area 1 as a whole, if a launch will use it
         bp.prev_words = x.L.area;
         bp.prev_n = t.total > 1 ? 1 : 0;
