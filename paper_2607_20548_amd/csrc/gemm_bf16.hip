@@ -491,14 +491,17 @@ __global__ __launch_bounds__(256) void axpby_bf16_kernel(float *__restrict__ W,
 
 }  // namespace
 
-// 256-tiles from half the compute units' count of them on, 16 iterations of
-// each: triangles of 136 tiles (4096 x 4096) take 5.65 ms in them and 7.11 in
-// 128-tiles, of 105 (3584 x 3584) 4.74 and 4.30; full products of 144
-// (3072 x 3072) 3.63 and 4.43, of 120 and 128 the same, of 100 (2560 x 2560)
-// 2.78 and 2.62, of 72 (1536 x 3072) 1.85 and 1.76.  64-tiles while 128-tiles
-// would leave compute units idle: 1024 x 1024 1.38 -> 0.79 ms, 1536 x 3072 2.21
-// -> 1.75; the same with a bound of 400 instead of 192.
-static constexpr int64_t MIN_TILES_256 = 128;
+// 256-tiles where 128-tiles would not all be resident at once (two per compute
+// unit), if they are themselves or hold at least 2.5 of those on average (small
+// and odd sides leave them half empty).  16 iterations in 256-tiles and in
+// 128-tiles: triangles of 528 128-tiles (4096 x 4096) 5.65 and 7.11 ms, of 406
+// (3584 x 3584) 4.74 and 4.30; full products of 576 (3072 x 3072) 3.63 and 4.43,
+// of 400 (2560 x 2560) 2.78 and 2.62; banks of 128 x (256 x 256), 384 and 512 of
+// them, 1.88 and 1.49; of 300 x (320 x 640), whose triangles hold 2 each,
+// 8.88 and 8.05; of 128 x (128 x 256) 1.25 and, in 64-tiles, 0.76.
+static constexpr int64_t ROUND_256 = 256, ROUND_128 = 512;
+// 64-tiles while 128-tiles would leave compute units idle: 1024 x 1024 1.38 ->
+// 0.79 ms, 1536 x 3072 2.21 -> 1.75; the same with a bound of 400.
 static constexpr int64_t MAX_TILES_64 = 192;
 
 hipError_t launch_gemm_bf16_nt(const BfGemmDesc &d, hipStream_t s) {
@@ -525,7 +528,12 @@ hipError_t launch_gemm_bf16_nt(const BfGemmDesc &d, hipStream_t s) {
                     (!d.D || (d.ldd % 8 == 0 && d.sD % 8 == 0 && al(d.D))) &&
                     (!d.Ct || (d.ldct % 8 == 0 && d.sCt % 8 == 0 && al(d.Ct)));
   tiles(T2);
-  if (wide && d.K > 0 && p.ntiles * d.batch >= MIN_TILES_256 && !(d.syrk && d.Ct)) {
+  const int64_t n256 = p.ntiles * d.batch;
+  tiles(128);
+  const int64_t n128 = p.ntiles * d.batch;
+  if (wide && d.K > 0 && n128 > ROUND_128 && (n256 <= ROUND_256 || 2 * n128 >= 5 * n256) &&
+      !(d.syrk && d.Ct)) {
+    tiles(T2);
     const dim3 grid(p.ntiles, 1, (unsigned)d.batch);
     const bool tail = p.K % KB != 0;
 #define SOAP_BF(MODE, TAIL) hipLaunchKernelGGL((gemm_bf16_nt256<MODE, TAIL>), grid, dim3(NTH), 0, s, p)
@@ -533,8 +541,7 @@ hipError_t launch_gemm_bf16_nt(const BfGemmDesc &d, hipStream_t s) {
     else { if (tail) SOAP_BF(BMODE_GENERAL, true); else SOAP_BF(BMODE_GENERAL, false); }
 #undef SOAP_BF
   } else {
-    tiles(128);
-    const bool few = p.ntiles * d.batch <= MAX_TILES_64;
+    const bool few = n128 <= MAX_TILES_64;
     if (few) tiles(64);
     const dim3 grid(p.ntiles, 1, (unsigned)d.batch);
 #define SOAP_BF(MODE, TB) hipLaunchKernelGGL((gemm_bf16_nt<MODE, TB>), grid, dim3(NTH), 0, s, p)

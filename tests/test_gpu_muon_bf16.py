@@ -193,11 +193,14 @@ def test_bf16_muon_fullsize_against_fp32_path():
 
 @pytest.mark.parametrize("batch,m,n", [(48, 264, 520), (48, 520, 264), (130, 256, 256),
                                        (44, 272, 1000), (130, 128, 72),
-                                       (130, 64, 256), (130, 264, 40)])
+                                       (130, 64, 256), (130, 264, 40),
+                                       (200, 248, 264), (200, 264, 248), (200, 200, 256),
+                                       (60, 520, 776), (64, 384, 384)])
 def test_tile_sizes_agree_bit_for_bit(batch, m, n):
-    """A batch large enough for 256-tiles (K a multiple of 64 and not, ragged
-    last tiles, mirrored triangles, a single slab) against its entries alone,
-    which take the small tiles: every tile size sums over k in the same order."""
+    """Batches that take 128- and 256-tiles (K a multiple of 64 and not, ragged
+    last tiles, mirrored triangles, triangles in one size and full products in
+    the other, a single slab) against their entries alone, which take the small
+    tiles: every tile size sums over k in the same order."""
     import torch
     import paper_2607_20548_amd as soap
     g = torch.Generator(device="cuda").manual_seed(m + n)
