@@ -251,11 +251,22 @@ struct SlabLoader {
   }
 };
 
-// Element (x, k) of an operand, k < K (used by the exact path below).
+// Four consecutive k of one row of an operand, from p on (used by the fp32
+// path below); those past `valid` are zero and not read.  p moves on by eight.
 template <bool KCONTIG>
-__device__ __forceinline__ float operand_at(const float *base, int64_t ld, int x, int k, int X) {
-  const int xc = min(x, X - 1);
-  return KCONTIG ? base[(int64_t)xc * ld + k] : base[(int64_t)k * ld + xc];
+__device__ __forceinline__ void exact_operand(const float *&p, int64_t ld, int valid, float (&e)[4]) {
+  const int64_t step = KCONTIG ? 1 : ld;
+  if (KCONTIG && valid >= 4) {
+    const f4u v = *reinterpret_cast<const f4u *>(p);
+    e[0] = v.x; e[1] = v.y; e[2] = v.z; e[3] = v.w;
+  } else {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      e[u] = 0.f;
+      if (u < valid) e[u] = p[u * step];
+    }
+  }
+  p += 8 * step;
 }
 
 // Maps the linear workgroup id to a (tile-row, tile-column) pair.
@@ -285,7 +296,7 @@ __device__ __forceinline__ void tile_coords(const KParams &p, int t, int &tm, in
 // blocks' slab sums, the slab in flight and the fragments of a block), whose
 // loads, splits and matrix instructions overlap one another; bounded to
 // three, the slab sums spill (180 -> 89 TFLOP/s).  Most V_ANY forms (odd sizes)
-// keep 8 to 20 bytes per lane in scratch even so: a few words moved per slab,
+// keep 8 to 44 bytes per lane in scratch even so: a few words moved per slab,
 // none among its matrix instructions.
 //
 // BT = 64 is for products with few tiles (four waves of one 32 x 32 block
@@ -397,8 +408,8 @@ __global__ __launch_bounds__(NTHREADS, BT == BIG ? 2 : 3) void gemm_f32_split(KP
   // A wave whose sums hold an infinity or a NaN (an infinite operand times a
   // zero part gives NaN here and not in fp32; operands from 2^111 and sums
   // from 2^96 on overflow by their scale) takes its sums again on the fp32
-  // matrix instructions, straight from memory (4096^3 of NaN: 2.7-4.0 ms, 35
-  // to 51 TFLOP/s); the others are scaled back.
+  // matrix instructions, straight from memory (4096^3 of NaN: 1.9-2.2 ms, 62
+  // to 72 TFLOP/s); the others are scaled back.
   {
     uint32_t mx = 0u;
 #pragma unroll
@@ -417,32 +428,52 @@ __global__ __launch_bounds__(NTHREADS, BT == BIG ? 2 : 3) void gemm_f32_split(KP
         for (int j = 0; j < NBLK; ++j)
 #pragma unroll
           for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-      constexpr int U = 4;   // pairs of k in flight
-#pragma unroll 1
-      for (int k = kbeg; k < kend; k += 2 * U) {
-        float ea[U][NBLK], eb[U][NBLK];
+      // Groups of 8 k: lane half h takes 4 consecutive ones, the next group
+      // is loaded while one is multiplied (not in the tile loop, whose own
+      // registers leave no room).
+      constexpr int BUFS = PERSIST ? 1 : 2;
+      const float *pa[NBLK], *pb[NBLK];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int kk = min(k + 2 * u + h, kend - 1);
+      for (int i = 0; i < NBLK; ++i) {
+        const int64_t xa = min(m0 + wm * WT + 32 * i + xl, p.M - 1), k4 = kbeg + 4 * h;
+        const int64_t xb = min(n0 + wn * WT + 32 * i + xl, p.N - 1);
+        pa[i] = A + (TA == 0 ? xa * p.lda + k4 : k4 * p.lda + xa);
+        pb[i] = B + (TB == 1 ? xb * p.ldb + k4 : k4 * p.ldb + xb);
+      }
+      float ea[BUFS][NBLK][4], eb[BUFS][NBLK][4];
+      auto fetch = [&](int f, int valid) {   // valid: k-values of this lane's four
 #pragma unroll
-          for (int i = 0; i < NBLK; ++i) {
-            ea[u][i] = operand_at<TA == 0>(A, p.lda, m0 + wm * WT + 32 * i + xl, kk, p.M);
-            eb[u][i] = operand_at<TB == 1>(B, p.ldb, n0 + wn * WT + 32 * i + xl, kk, p.N);
-          }
+        for (int i = 0; i < NBLK; ++i) {
+          exact_operand<TA == 0>(pa[i], p.lda, valid, ea[f][i]);
+          exact_operand<TB == 1>(pb[i], p.ldb, valid, eb[f][i]);
         }
+      };
+      auto multiply = [&](int f) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const bool live = k + 2 * u + h < kend;
-#pragma unroll
-          for (int i = 0; i < NBLK; ++i) {
-            ea[u][i] = live ? ea[u][i] : 0.f;
-            eb[u][i] = live ? eb[u][i] : 0.f;
-          }
+        for (int u = 0; u < 4; ++u)
 #pragma unroll
           for (int i = 0; i < NBLK; ++i)
 #pragma unroll
             for (int j = 0; j < NBLK; ++j)
-              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(ea[u][i], eb[u][j], acc[i][j], 0, 0, 0);
+              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(ea[f][i][u], eb[f][j][u], acc[i][j],
+                                                              0, 0, 0);
+      };
+      const int groups = (kend - kbeg + 7) / 8;
+      auto valid = [&](int g) { return kend - kbeg - 8 * g - 4 * h; };
+      if constexpr (BUFS == 1) {
+#pragma unroll 1
+        for (int g = 0; g < groups; ++g) {
+          fetch(0, valid(g));
+          multiply(0);
+        }
+      } else {
+        fetch(0, valid(0));
+#pragma unroll 1
+        for (int g = 0; g < groups; g += 2) {
+          if (g + 1 < groups) fetch(1, valid(g + 1));
+          multiply(0);
+          if (g + 2 < groups) fetch(0, valid(g + 2));
+          if (g + 1 < groups) multiply(1);
         }
       }
     }

@@ -103,19 +103,23 @@ def test_small_operands_beside_ordinary_ones(soap, ta, tb, M, N, K):
     assert (err <= limit).all(), float((err / limit).max())
 
 
-def test_sums_past_the_scaled_range(soap):
-    """Sums near 1e30 and 1e36 (finite, but not when scaled): taken on the fp32
-    instructions, odd K included."""
+@pytest.mark.parametrize("ta", [0, 1])
+@pytest.mark.parametrize("tb", [0, 1])
+@pytest.mark.parametrize("M,N,K,shift", [(140, 130, 77, 1), (1, 3, 2, 0), (65, 64, 96, 0),
+                                         (1801, 2051, 65, 3), (2048, 1792, 48, 0)])
+def test_sums_past_the_scaled_range(soap, ta, tb, M, N, K, shift):
+    """Sums near 1e30 and 1e36 (finite, but not when scaled) are taken on the
+    fp32 instructions: every layout, whole and ragged groups of k."""
     import torch
     for scale in (1e15, 1e18):
-        A, pa, lda, ah = operand(140, 77, 0, 0, 1, scale)
-        B, pb, ldb, bh = operand(77, 130, 0, 0, 2, scale)
-        C = torch.empty(140, 130, device="cuda")
-        soap.soap_gemm_f32(0, 0, 140, 130, 77, 1.0, pa, lda, pb, ldb, 0.0, C, 130)
-        want = ah @ bh
+        A, pa, lda, ah = operand(*((K, M) if ta else (M, K)), 0, shift, 1, scale)
+        B, pb, ldb, bh = operand(*((N, K) if tb else (K, N)), 0, shift, 2, scale)
+        C = torch.empty(M, N, device="cuda")
+        soap.soap_gemm_f32(ta, tb, M, N, K, 1.0, pa, lda, pb, ldb, 0.0, C, N)
+        want = (ah.T if ta else ah) @ (bh.T if tb else bh)
         got = C.cpu().numpy().astype(np.float64)
         # fp32 accumulation in order: sqrt(K) roundings of 2^-24, four times that
-        assert np.linalg.norm(got - want) / np.linalg.norm(want) <= 4 * 2.0 ** -24 * 77 ** 0.5
+        assert np.linalg.norm(got - want) / np.linalg.norm(want) <= 4 * 2.0 ** -24 * K ** 0.5
 
 
 def test_infinite_and_huge_operands(soap):
